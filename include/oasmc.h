@@ -413,7 +413,7 @@ int oasmc_resample(oasmc_handle* h, int64_t N, const double* lw, uint32_t u, int
  * systematic resampling as oasmc_resample, with the same kernels and bitwise
  * the same ancestors, but its scratch (integer CDF, block totals, flag words)
  * is a fixed static device array of about 8.0 MiB (OASMC_NOALLOC_MAX_N
- * uint64 words plus 4 KiB), one copy per GPU, held until the process ends.
+ * uint64 words plus 8 KiB), one copy per GPU, held until the process ends.
  * No handle; runs on the current HIP device, whose scratch address is looked
  * up on the first call on that device.  lw[N] (device, binary64) and anc[N]
  * (device, int32) are the caller's; N must lie in [1, OASMC_NOALLOC_MAX_N]

@@ -153,16 +153,15 @@ struct AsmcState {
     // scalars updated on the device
     double* scal;      // [0] log Z_hat, [1] max(lw) at event, [2] flag, [3] u word
     int* nres;         // [1]
-    unsigned* ticket;  // [2] arrival counters of the per-step merge and of the
-                       // resampler's scan; zero between launches (the last
-                       // arriving block resets its counter)
+    unsigned* ticket;  // arrival counter of the per-step merge; zero between
+                       // launches (the last arriving block resets it)
     double* log_g;     // [3*T] device
     double* ess;       // [T]
     int* resampled;    // [T]
     double* accept;    // [T] accepted count
     // resampler scratch
     uint64_t* C;       // [N] block-local inclusive prefix of q
-    uint64_t* btot;    // [nblocks] inclusive block totals after the scan
+    uint64_t* btot;    // [nblocks] block totals
 };
 
 // Final-iteration rejuvenation (Sec. "Computing expectations"): N chains of
@@ -327,7 +326,10 @@ hipError_t launch_round_schedule(const RoundDev* rd, int nprob, hipStream_t st);
 hipError_t launch_philox(uint64_t seed, const uint32_t* ctr, uint32_t* out, int64_t count,
                          hipStream_t st);
 
+// Blocks of the resampler's scan, and the 64-bit words of its btot scratch
+// (block totals, then the block maxima of the plain call).
 int64_t resample_blocks(int64_t N);
+inline int64_t resample_words(int64_t N) { return 2 * resample_blocks(N); }
 
 // One logistic-regression problem as its sweep kernel sees it.
 struct LogregArgs {

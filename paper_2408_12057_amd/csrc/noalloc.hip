@@ -15,12 +15,13 @@ using namespace oasmc;
 namespace {
 
 // Layout of the scratch array: C[kNoAllocMaxN] (uint64), then the block totals
-// (uint64, one per scan block of the largest N), then 8 binary64 flag words.
+// and block maxima (one 64-bit word each per scan block of the largest N), then
+// 8 binary64 flag words.
 constexpr int64_t kNoAllocMaxN = OASMC_NOALLOC_MAX_N;
-constexpr int64_t kMaxScanBlocks = 512;  // resample_blocks(kNoAllocMaxN), checked below
+constexpr int64_t kMaxScanWords = 1024;  // resample_words(kNoAllocMaxN), checked below
 constexpr size_t kOffC = 0;
 constexpr size_t kOffBtot = kOffC + (size_t)kNoAllocMaxN * sizeof(uint64_t);
-constexpr size_t kOffScal = kOffBtot + (size_t)kMaxScanBlocks * sizeof(uint64_t);
+constexpr size_t kOffScal = kOffBtot + (size_t)kMaxScanWords * sizeof(uint64_t);
 constexpr size_t kScratchBytes = kOffScal + 8 * sizeof(double);
 
 constexpr int kMaxDevices = 64;
@@ -67,7 +68,7 @@ extern "C" int oasmc_resample_noalloc(int64_t N, const double* lw, uint32_t u, i
     if (N < 1 || N > kNoAllocMaxN)
         return record_error(OASMC_EINVAL, "N must lie in [1, %lld] (size of the static scratch)",
                      (long long)kNoAllocMaxN);
-    if (resample_blocks(kNoAllocMaxN) > kMaxScanBlocks)
+    if (resample_words(kNoAllocMaxN) > kMaxScanWords)
         return record_error(OASMC_EINVAL, "scratch layout too small for the scan blocks");
     void* base = nullptr;
     const int rc = scratch_ptr(&base);

@@ -1113,7 +1113,7 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
         HIP_TRY(wget(h, B_ESS, T, &z.ess));
         HIP_TRY(wget(h, B_RES, T, &z.resampled));
         HIP_TRY(wget(h, B_C, N, &z.C));
-        HIP_TRY(wget(h, B_BTOT, resample_blocks(N), &z.btot));
+        HIP_TRY(wget(h, B_BTOT, resample_words(N), &z.btot));
         z.ticket = reinterpret_cast<unsigned*>(z.nres + 1);  // cleared with nres below
         z.scal = dscal;
         z.log_g = dlogg;
@@ -1451,7 +1451,7 @@ int oasmc_rejuvenate(oasmc_handle* h, const oasmc_problem* problem, const oasmc_
     HIP_TRY(wget(h, B_RJ_OUT, 2 * (size_t)d + 1, &res));
     HIP_TRY(wget(h, B_SCAL, 8, &scal));
     HIP_TRY(wget(h, B_C, N, &C));
-    HIP_TRY(wget(h, B_BTOT, resample_blocks(N), &btot));
+    HIP_TRY(wget(h, B_BTOT, resample_words(N), &btot));
     R.anc = anc;
     R.tsum = tsum;
     HIP_TRY(launch_resample_event(N, lw, R.a.key, (uint32_t)T, anc, C, btot, scal, st));
@@ -1674,7 +1674,7 @@ int oasmc_resample(oasmc_handle* h, int64_t N, const double* lw, uint32_t u, int
     uint64_t *C, *bt;
     double* scal;
     HIP_TRY(wget(h, B_C, N, &C));
-    HIP_TRY(wget(h, B_BTOT, resample_blocks(N), &bt));
+    HIP_TRY(wget(h, B_BTOT, resample_words(N), &bt));
     HIP_TRY(wget(h, B_SCAL, 8, &scal));
     HIP_TRY(launch_resample_plain(N, lw, u, anc, C, bt, scal, st));
     double flag[4];
