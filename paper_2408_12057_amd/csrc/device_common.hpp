@@ -158,6 +158,19 @@ __device__ __forceinline__ double group_sum(double v)
     return v;
 }
 
+// Largest value of aligned groups of G lanes, by the same moves.
+template <int G>
+__device__ __forceinline__ double group_max(double v)
+{
+    if constexpr (G >= 2) v = fmax(v, dpp_f64<kDppXor1>(v));
+    if constexpr (G >= 4) v = fmax(v, dpp_f64<kDppXor2>(v));
+    if constexpr (G >= 8) v = fmax(v, dpp_f64<kDppHalfMirror>(v));
+    if constexpr (G >= 16) v = fmax(v, dpp_f64<kDppMirror>(v));
+#pragma unroll
+    for (int o = 16; o < G; o <<= 1) v = fmax(v, __shfl_xor(v, o, kWave));
+    return v;
+}
+
 // Wave-wide max and sum (xor butterflies: every lane ends with the same bits).
 __device__ __forceinline__ double wave_max(double v)
 {

@@ -770,62 +770,179 @@ hipError_t launch_asmc_move(const SweepArgs& a, const ValuShape& s, const AsmcSt
 // (beta_{t-1}, 1] keeping the upper part while CESS >= rho N.  This is the
 // per-step communication across all particles that the loop-swapped OAIS pass
 // avoids.
+//
+// Bound by latency: one workgroup, so that no launch or grid barrier stands
+// between two evaluations of log CESS.  Three things keep them few and short
+// (2^14 particles on the Unid target, a step's choice: 742 -> 30 us):
+//  * CESS(b) falls with b (log CESS has the derivative 2 (E_1 - E_2) of the mean
+//    of ell under w exp(i (b - b_0) ell), which grows with i), so the halvings'
+//    decisions follow from one point on either side of the crossing: a secant on
+//    sqrt(-log(CESS / N)), nearly linear in b - b_0, finds the crossing, the
+//    halvings are walked without evaluating, and the two ends of the last
+//    interval are evaluated as they would have been.  Seven evaluations instead of
+//    42; where one of the two disagrees (rounding at the crossing), the halvings go
+//    on from the known points by evaluation.
+//  * particles without weight (log w or ell = -inf: nine in ten on Unid) add
+//    nothing, and the others are kept in LDS where they fit;
+//  * one barrier an evaluation: each wave's maximum and its sum against it,
+//    merged by every wave.
 // ---------------------------------------------------------------------------
 constexpr int kZjaThreads = 1024;
+constexpr int kZjaWaves = kZjaThreads / kWave;
+constexpr int kZjaHeld = 8192;  // particles held in LDS (128 KB)
 
-// Log-sum-exps L_i over the particles of log w + i a ell for i = I0 .. 2, in
-// two passes (a block maximum, then a block sum of exp(x - max): one
-// exponential per term, no data-dependent branch around it); per-thread
-// partials in particle order, then the wave's xor butterfly, then the waves in
-// order, so every thread ends with the same bits.
-template <int I0>
-__device__ __forceinline__ void zja_lse(int64_t N, const double* __restrict__ lw,
-                                        const double* __restrict__ ell, double a, double (&L)[3],
-                                        double* shm)
+// Two log-sum-exps at once from a wave's maxima m and sums s of exp against them,
+// merged over the workgroup's waves (every thread ends with the same bits): row
+// of 16 lanes 2 i reads the waves' entries of sum i, so the exponentials and the
+// logarithm of both are formed together.  part: an entry per wave; the caller
+// alternates two of them, so that one barrier separates a write from the reads
+// two calls earlier.
+struct ZjaPart {
+    double2 v[2][kZjaWaves];
+};
+
+__device__ __forceinline__ void zja_merge(const double (&m)[2], const double (&s)[2], double (&L)[2],
+                                          ZjaPart& part)
 {
-    constexpr int NW = kZjaThreads / kWave;
+    static_assert(kZjaWaves == 16, "a row of 16 lanes holds one entry per wave");
     const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    auto term = [&](int64_t j, int i) {
-        const double v = lw[j];
-        return (i == 0) ? v : v + (double)i * a * ell[j];
+    if (lane < 2) part.v[lane][w] = lane == 0 ? make_double2(m[0], s[0]) : make_double2(m[1], s[1]);
+    __syncthreads();
+    const double2 e = part.v[lane / 32][lane % 16];
+    const double M = group_max<16>(e.x);
+    const double v = lse_value(M, group_sum<16>((e.x > -INFINITY) ? e.y * exp(e.x - M) : 0.0));
+    L[0] = __shfl(v, 0, kWave);
+    L[1] = __shfl(v, 32, kWave);
+}
+
+// log sum_n exp(log w_n), and the particles with weight into `held` in order
+// while they fit (count: how many there are).  Up to 16 particles a thread are
+// read once and stay in registers.
+__device__ __forceinline__ double zja_gather(int64_t N, const double* __restrict__ lw,
+                                             const double* __restrict__ ell, double2* held,
+                                             int64_t& count, ZjaPart& part, int64_t (*cnt)[2])
+{
+    constexpr int kRegs = 16;
+    const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int64_t per = (N + kZjaThreads - 1) / kZjaThreads * kWave;  // particles of a wave
+    const int64_t j0 = w * per, j1 = (j0 + per < N) ? j0 + per : N;
+    const bool once = per <= kRegs * kWave;
+    double m[2] = {-INFINITY, -INFINITY}, s[2] = {0.0, 0.0}, L[2];
+    double v[kRegs], e[kRegs];
+    int64_t mine = 0, heavy = 0;  // with weight, and with log w > -inf
+    auto look = [&](double lv, double le) {
+        m[0] = fmax(m[0], lv);
+        mine += __popcll(__ballot(lv > -INFINITY && le > -INFINITY));
+        heavy += __popcll(__ballot(lv > -INFINITY));
     };
-    double m[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t j = threadIdx.x; j < N; j += kZjaThreads)
+    if (once) {
 #pragma unroll
-        for (int i = I0; i < 3; ++i) m[i] = fmax(m[i], term(j, i));
-#pragma unroll
-    for (int i = I0; i < 3; ++i) {
-        m[i] = wave_max(m[i]);
-        if (lane == 0) shm[w * 3 + i] = m[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = I0; i < 3; ++i) {
-        double mm = -INFINITY;
-        for (int ww = 0; ww < NW; ++ww) mm = fmax(mm, shm[ww * 3 + i]);
-        m[i] = mm;
-    }
-    __syncthreads();
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int64_t j = threadIdx.x; j < N; j += kZjaThreads)
-#pragma unroll
-        for (int i = I0; i < 3; ++i) {
-            const double x = term(j, i);
-            s[i] += (x > -INFINITY) ? exp(x - m[i]) : 0.0;
+        for (int k = 0; k < kRegs; ++k) {
+            const int64_t j = j0 + k * kWave + lane;
+            v[k] = (j < j1) ? lw[j] : -INFINITY;
+            e[k] = (j < j1) ? ell[j] : -INFINITY;
         }
 #pragma unroll
-    for (int i = I0; i < 3; ++i) {
-        s[i] = wave_sum(s[i]);
-        if (lane == 0) shm[w * 3 + i] = s[i];
+        for (int k = 0; k < kRegs; ++k) look(v[k], e[k]);
+    } else {
+        for (int64_t b = j0; b < j1; b += kWave) {
+            const int64_t j = b + lane;
+            look((j < j1) ? lw[j] : -INFINITY, (j < j1) ? ell[j] : -INFINITY);
+        }
+    }
+    m[0] = group_max<kWave>(m[0]);
+    if (lane == 0) {
+        cnt[w][0] = mine;
+        cnt[w][1] = heavy;
     }
     __syncthreads();
+    int64_t at = 0, all = 0;
+    count = 0;
 #pragma unroll
-    for (int i = I0; i < 3; ++i) {
-        double ss = 0.0;
-        for (int ww = 0; ww < NW; ++ww) ss += shm[ww * 3 + i];
-        L[i] = (m[i] > -INFINITY) ? lse_value(m[i], ss) : -INFINITY;
+    for (int i = 0; i < kZjaWaves; ++i) {
+        if (i < w) at += cnt[i][0];
+        count += cnt[i][0];
+        all += cnt[i][1];
     }
-    __syncthreads();  // shm is reused by the next call
+    const bool fits = count <= kZjaHeld;
+    // where every weight is held, the sum of the weights runs over the held
+    const bool held_sum = fits && all == count;
+    auto put = [&](double lv, double le) {
+        const bool on = lv > -INFINITY && le > -INFINITY;
+        const uint64_t bal = __ballot(on);
+        if (on && fits) held[at + __popcll(bal & (((uint64_t)1 << lane) - 1))] = make_double2(lv, le);
+        at += __popcll(bal);
+        if (!held_sum) s[0] += (lv > -INFINITY) ? exp(lv - m[0]) : 0.0;
+    };
+    if (once) {
+#pragma unroll
+        for (int k = 0; k < kRegs; ++k) put(v[k], e[k]);
+    } else {
+        for (int64_t b = j0; b < j1; b += kWave) {
+            const int64_t j = b + lane;
+            put((j < j1) ? lw[j] : -INFINITY, (j < j1) ? ell[j] : -INFINITY);
+        }
+    }
+    if (held_sum) {
+        __syncthreads();
+        m[0] = -INFINITY;
+        for (int j = threadIdx.x; j < (int)count; j += kZjaThreads) m[0] = fmax(m[0], held[j].x);
+        m[0] = group_max<kWave>(m[0]);
+        for (int j = threadIdx.x; j < (int)count; j += kZjaThreads) s[0] += exp(held[j].x - m[0]);
+    }
+    s[0] = group_sum<kWave>(s[0]);
+    zja_merge(m, s, L, part);
+    return L[0];
+}
+
+// log sum_n exp(log w_n + i a ell_n), i = 1, 2, over the particles with weight:
+// the held ones, or all of them from memory.
+__device__ __forceinline__ void zja_lse(int64_t n, const double2* held, int64_t N,
+                                        const double* __restrict__ lw, const double* __restrict__ ell,
+                                        double a, double (&L)[2], ZjaPart& part)
+{
+    double m[2] = {-INFINITY, -INFINITY}, s[2] = {0.0, 0.0};
+    auto pass = [&](auto&& f) {
+        if (n <= kZjaHeld) {
+            for (int j = threadIdx.x; j < (int)n; j += kZjaThreads) {
+                const double2 v = held[j];
+                f(v.x + a * v.y, v.x + 2.0 * a * v.y);
+            }
+        } else {
+            for (int64_t j = threadIdx.x; j < N; j += kZjaThreads) {
+                const double v = lw[j], e = ell[j];
+                f(v + a * e, v + 2.0 * a * e);
+            }
+        }
+    };
+    pass([&](double x1, double x2) {
+        m[0] = fmax(m[0], x1);
+        m[1] = fmax(m[1], x2);
+    });
+    m[0] = group_max<kWave>(m[0]);
+    m[1] = group_max<kWave>(m[1]);
+    pass([&](double x1, double x2) {
+        s[0] += (x1 > -INFINITY) ? exp(x1 - m[0]) : 0.0;
+        s[1] += (x2 > -INFINITY) ? exp(x2 - m[1]) : 0.0;
+    });
+    s[0] = group_sum<kWave>(s[0]);
+    s[1] = group_sum<kWave>(s[1]);
+    zja_merge(m, s, L, part);
+}
+
+// The halvings of (b0, 1], the upper part kept where its start lies at most r
+// from b0: the last interval (lo, hi].  A crossing estimate r between a known
+// point where CESS is enough and one where it is not gives their decisions too.
+__device__ __forceinline__ void zja_walk(double b0, int iters, double r, double& lo, double& hi)
+{
+    lo = b0;
+    hi = 1.0;
+    for (int it = 0; it < iters; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        const bool up = mid - b0 <= r;
+        lo = up ? mid : lo;
+        hi = up ? hi : mid;
+    }
 }
 
 __global__ void __launch_bounds__(kZjaThreads)
@@ -834,31 +951,82 @@ __global__ void __launch_bounds__(kZjaThreads)
                  double* log_g)
 {
     if (t > *stop) return;
-    __shared__ double shm[(kZjaThreads / kWave) * 3];
+    extern __shared__ __align__(16) char sh_zja[];
+    double2* held = reinterpret_cast<double2*>(sh_zja);
+    __shared__ ZjaPart part[2];
+    __shared__ int64_t cnt[kZjaWaves][2];
     const double b0 = beta[t - 1];
-    double L[3];
-    zja_lse<0>(N, lw, ell, 1.0 - b0, L, shm);  // L_0 (log of sum w_{t-1}) is fixed for the step
-    const double L0 = L[0];
-    double bt;
-    if (2.0 * L[1] - L[2] - L0 >= log_rho) {
-        bt = 1.0;
-    } else {
-        double lo = b0, hi = 1.0;
-        for (int it = 0; it < iters; ++it) {
-            const double mid = 0.5 * (lo + hi);
-            zja_lse<1>(N, lw, ell, mid - b0, L, shm);
-            if (2.0 * L[1] - L[2] - L0 >= log_rho) lo = mid;
-            else hi = mid;
+    const double prev = (t >= 2) ? b0 - beta[t - 2] : 1.0;
+    int64_t n;
+    const double L0 = zja_gather(N, lw, ell, held, n, part[0], cnt);  // fixed for the step
+    double L[2], lx = -1.0;  // the moments at the offset lx
+    int flip = 1;
+    auto log_cess = [&](double x) {
+        zja_lse(n, held, N, lw, ell, x, L, part[flip]);
+        flip ^= 1;
+        lx = x;
+        return 2.0 * L[0] - L[1] - L0;
+    };
+    const double full = 1.0 - b0;
+    double bt = 1.0;
+    if (t < Tmax) {
+        // known: enough at klo, not at khi
+        double klo = 0.0, khi = INFINITY;
+        const double tg = sqrt(-log_rho), cell = ldexp(full, -iters);
+        double xa = 0.0, ga = 0.0, r = (prev < full) ? prev : full;
+        for (int ev = 0; ev < 10; ++ev) {
+            const double F = log_cess(r);
+            if (F >= log_rho) {
+                klo = r;
+                if (r == full) break;
+            } else {
+                khi = r;
+            }
+            const double g = sqrt(fmax(-F, 0.0)), last = r;
+            const bool near = fabs(g - tg) < 0.5 * tg && fabs(ga - tg) < 0.5 * tg && g != ga;
+            r = near ? last + (tg - g) * (last - xa) / (g - ga) : last * tg / g;
+            xa = last;
+            ga = g;
+            if (!(r < full) && khi == INFINITY) r = full;  // beta = 1 may be enough
+            else if (!(r > klo && r < khi)) r = 0.5 * (klo + fmin(khi, full));
+            if (fabs(r - last) < 0.25 * cell) break;
         }
-        bt = (lo > b0) ? lo : hi;
+        if (klo < full) {
+            double lo, hi;
+            zja_walk(b0, iters, r, lo, hi);
+            // the upper end first: the lower one is the step's beta
+            bool wrong = false;
+            if (hi - b0 < khi) {
+                wrong = log_cess(hi - b0) >= log_rho;
+                if (wrong) klo = hi - b0;
+                else khi = hi - b0;
+            }
+            if (!wrong && lo - b0 > klo) {
+                wrong = !(log_cess(lo - b0) >= log_rho);
+                if (wrong) khi = lo - b0;
+                else klo = lo - b0;
+            }
+            if (wrong) {  // the known points decide what they can, evaluation the rest
+                if (khi > full) khi = log_cess(full) >= log_rho ? INFINITY : full;
+                lo = b0;
+                hi = 1.0;
+                for (int it = 0; khi <= full && it < iters; ++it) {
+                    const double mid = 0.5 * (lo + hi), x = mid - b0;
+                    if (x <= klo || (x < khi && log_cess(x) >= log_rho)) lo = mid;
+                    else hi = mid;
+                }
+                bt = khi > full ? 1.0 : (lo > b0) ? lo : hi;
+            } else {
+                bt = (lo > b0) ? lo : hi;
+            }
+        }
     }
-    if (t == Tmax) bt = 1.0;
-    zja_lse<1>(N, lw, ell, bt - b0, L, shm);  // the step's moments at the chosen beta_t
-    L[0] = L0;
+    if (lx != bt - b0) (void)log_cess(bt - b0);  // the step's moments at the chosen beta_t
     if (threadIdx.x == 0) {
         beta[t] = bt;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) log_g[(size_t)i * Tmax + (t - 1)] = L[i];
+        log_g[t - 1] = L0;
+        log_g[(size_t)Tmax + (t - 1)] = L[0];
+        log_g[(size_t)2 * Tmax + (t - 1)] = L[1];
         if (bt >= 1.0) *stop = t;
     }
 }
@@ -866,9 +1034,14 @@ __global__ void __launch_bounds__(kZjaThreads)
 __global__ void __launch_bounds__(kZjaThreads) k_zja_final(int64_t N, const double* lw,
                                                            double* logZ)
 {
-    __shared__ double shm[(kZjaThreads / kWave) * 3];
-    double L[3];
-    zja_lse<0>(N, lw, lw, 0.0, L, shm);
+    __shared__ ZjaPart part;
+    double m[2] = {-INFINITY, -INFINITY}, s[2] = {0.0, 0.0}, L[2];
+    for (int64_t j = threadIdx.x; j < N; j += kZjaThreads) m[0] = fmax(m[0], lw[j]);
+    m[0] = group_max<kWave>(m[0]);
+    for (int64_t j = threadIdx.x; j < N; j += kZjaThreads)
+        s[0] += (lw[j] > -INFINITY) ? exp(lw[j] - m[0]) : 0.0;
+    s[0] = group_sum<kWave>(s[0]);
+    zja_merge(m, s, L, part);
     if (threadIdx.x == 0) logZ[0] = L[0] - log((double)N);
 }
 
@@ -876,7 +1049,11 @@ hipError_t launch_zja_select(int64_t N, const double* lw, const double* ell, dou
                              int Tmax, double log_rho, int iters, int* stop, double* log_g,
                              hipStream_t st)
 {
-    hipLaunchKernelGGL(k_zja_select, dim3(1), dim3(kZjaThreads), 0, st, N, lw, ell, beta, t, Tmax,
+    const size_t shb = sizeof(double2) * (size_t)std::min<int64_t>(N, kZjaHeld);
+    const hipError_t e = hipFuncSetAttribute((const void*)k_zja_select,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shb);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_zja_select, dim3(1), dim3(kZjaThreads), shb, st, N, lw, ell, beta, t, Tmax,
                        log_rho, iters, stop, log_g);
     return hipGetLastError();
 }
