@@ -40,7 +40,8 @@ __global__ void __launch_bounds__(256, (AdjMinWaves<DPL, KB>::value)) k_adjoint_
     using PT = Particle<kGmm, LPP, DPL>;
     const SweepArgs& a = A.a;
     extern __shared__ __align__(16) char sh_dyn[];
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn);
+    __shared__ NormalTables sh_nt;
+    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;

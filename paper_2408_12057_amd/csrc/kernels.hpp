@@ -43,6 +43,7 @@ struct TargetDev {
 // (k, j, r) at (k DPL + j) LPP + r is coordinate r DPL + j of mean k, zero
 // beyond d, so a wave reads them without bank conflicts and padded
 // coordinates need no branch.
+struct NormalTables;
 struct ParView {
     const float* m;
     const float* mu;
@@ -50,6 +51,7 @@ struct ParView {
     const double* iv;
     const double* lm;   // [DPL][LPP]
     const double* lmu;  // [K or 1][DPL][LPP]
+    const NormalTables* nt;  // LDS of the workgroup (null in a stored view)
 };
 
 // Mixture components handled together by the particle code (the lane layout

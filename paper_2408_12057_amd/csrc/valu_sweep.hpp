@@ -20,6 +20,7 @@
 //    unless the trigger fired).
 #pragma once
 #include "kernels.hpp"
+#include "normal_math.hpp"
 
 namespace oasmc {
 
@@ -79,7 +80,7 @@ __device__ __forceinline__ ParView stage_params(const TargetDev& tg, char* sh)
         iv[k] = on ? 1.0 / v : 0.0;
     }
     __syncthreads();
-    return ParView{m, mu, hv, iv};
+    return ParView{m, mu, hv, iv, nullptr, nullptr, nullptr};
 }
 
 inline size_t params_bytes(const TargetDev& tg)
@@ -90,16 +91,17 @@ inline size_t params_bytes(const TargetDev& tg)
 
 
 // The same staging followed by the binary64 lane-layout means lm, lmu of the
-// shape (LPP, DPL).
+// shape (LPP, DPL) and the tables of the normals.
 template <int LPP, int DPL>
-__device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char* sh)
+__device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char* sh, NormalTables& nt)
 {
+    stage_tables(nt);
     const ParView base = stage_params(tg, sh);
     double* lane = reinterpret_cast<double*>(sh + lane_params_offset(tg));
     const int nl = (int)lane_param_doubles(tg, LPP, DPL);
     for (int e = threadIdx.x; e < nl; e += blockDim.x) lane[e] = lane_param(tg, LPP, DPL, e);
     __syncthreads();
-    return ParView{base.m, base.mu, base.hiv, base.iv, lane, lane + LPP * DPL};
+    return ParView{base.m, base.mu, base.hiv, base.iv, lane, lane + LPP * DPL, &nt};
 }
 
 
@@ -313,9 +315,9 @@ struct Particle {
     // uniform branch; with several lanes per particle the block index differs
     // across the wave, the branch would diverge (no saving) and its extra live
     // values cost the wide layouts registers, so the pair is always formed.
-    static __device__ __forceinline__ void normals_block(const RngKey& key, uint32_t n,
-                                                         uint32_t t, uint32_t stream, int r,
-                                                         int d, int bb, double (&q)[4],
+    static __device__ __forceinline__ void normals_block(const ParView& pv, const RngKey& key,
+                                                         uint32_t n, uint32_t t, uint32_t stream,
+                                                         int r, int d, int bb, double (&q)[4],
                                                          uint32_t substep = 0u)
     {
         static_assert(DPL % 4 == 0, "lane slices are whole blocks of 4 coordinates");
@@ -323,21 +325,25 @@ struct Particle {
 #pragma unroll
         for (int u = 0; u < 4; ++u) q[u] = 0.0;
         if (4 * b < d) {
-            double w[4];
-            normals4(key, n, t, stream, (uint32_t)b, w, substep, LPP == 1 ? d - 4 * b : 4);
+            double z[4];
+            const uint4 w = draw_block(key, n, t, stream, substep, (uint32_t)b);
+            box_muller(*pv.nt, w.x, w.y, z[0], z[1]);
+            z[2] = z[3] = 0.0;
+            if (LPP > 1 || d - 4 * b > 2) box_muller(*pv.nt, w.z, w.w, z[2], z[3]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) q[u] = (4 * b + u < d) ? w[u] : 0.0;
+            for (int u = 0; u < 4; ++u) q[u] = (4 * b + u < d) ? z[u] : 0.0;
         }
     }
 
     // d normals of one (particle, step, stream) split over the group's lanes.
-    static __device__ __forceinline__ void normals(const RngKey& key, uint32_t n, uint32_t t,
-                                                   uint32_t stream, int r, int d, double (&z)[DPL])
+    static __device__ __forceinline__ void normals(const ParView& pv, const RngKey& key, uint32_t n,
+                                                   uint32_t t, uint32_t stream, int r, int d,
+                                                   double (&z)[DPL])
     {
 #pragma unroll
         for (int bb = 0; bb < DPL / 4; ++bb) {
             double q[4];
-            normals_block(key, n, t, stream, r, d, bb, q);
+            normals_block(pv, key, n, t, stream, r, d, bb, q);
 #pragma unroll
             for (int u = 0; u < 4; ++u) z[4 * bb + u] = q[u];
         }
@@ -362,7 +368,7 @@ struct Particle {
             return eval<false>(tg, c, pv, r, x, g);
         }
         double z[DPL];
-        normals(key, n, 0u, kStreamInit, r, tg.d, z);
+        normals(pv, key, n, 0u, kStreamInit, r, tg.d, z);
 #pragma unroll
         for (int j = 0; j < DPL; ++j) {
             x[j] = (float)(ref(pv, r, j) + c.sref * z[j]);
@@ -399,7 +405,7 @@ struct Particle {
 #pragma unroll
                 for (int bb = 0; bb < DPL / 4; ++bb) {
                     double q[4];
-                    normals_block(key, n, t, kStreamMove, r, tg.d, bb, q, (uint32_t)sub);
+                    normals_block(pv, key, n, t, kStreamMove, r, tg.d, bb, q, (uint32_t)sub);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         const int j = 4 * bb + u;
@@ -418,7 +424,7 @@ struct Particle {
                 else
                     la = group_sum<LPP>(dle) * c.half_inv_s2r + beta * (ellq - ell);
                 const uint4 w = draw_block(key, n, t, kStreamAccept, (uint32_t)sub, 0u);
-                const bool acc = (forced >= 0) ? (forced != 0) : (log(word_uniform(w.x)) < la);
+                const bool acc = (forced >= 0) ? (forced != 0) : (-0.5 * minus2_log_word(*pv.nt, w.x) < la);
                 if (acc) {
 #pragma unroll
                     for (int j = 0; j < DPL; ++j) x[j] = xq[j];
@@ -429,7 +435,7 @@ struct Particle {
             return any;
         }
         double z[DPL];
-        if constexpr (uses_grad(MOVE)) normals(key, n, t, kStreamMove, r, tg.d, z);
+        if constexpr (uses_grad(MOVE)) normals(pv, key, n, t, kStreamMove, r, tg.d, z);
         float xp[DPL];
         double gp[DPL];
         double ellp;
@@ -439,7 +445,7 @@ struct Particle {
 #pragma unroll
             for (int bb = 0; bb < DPL / 4; ++bb) {
                 double q[4];
-                normals_block(key, n, t, kStreamMove, r, tg.d, bb, q);
+                normals_block(pv, key, n, t, kStreamMove, r, tg.d, bb, q);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int j = 4 * bb + u;
@@ -514,7 +520,7 @@ struct Particle {
                         group_sum<LPP>(kin1) + group_sum<LPP>(kin0);
         }
         const uint4 w = draw_block(key, n, t, kStreamAccept, 0u, 0u);
-        const bool acc = (forced >= 0) ? (forced != 0) : (log(word_uniform(w.x)) < log_alpha);
+        const bool acc = (forced >= 0) ? (forced != 0) : (-0.5 * minus2_log_word(*pv.nt, w.x) < log_alpha);
         if (acc) {
 #pragma unroll
             for (int j = 0; j < DPL; ++j) {
@@ -726,7 +732,8 @@ __global__ void __launch_bounds__(256) k_oais_valu(SweepArgs a)
     __shared__ double2 sh_rec[kWavesPerBlock][kTC][kWave / LPP];
     __shared__ uint32_t sh_cnt[kWavesPerBlock][kTC];
     extern __shared__ __align__(16) char sh_dyn[];
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn);
+    __shared__ NormalTables sh_nt;
+    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
     const Consts c = make_consts(a.tg);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform
     const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + wv;
@@ -746,6 +753,9 @@ __global__ void __launch_bounds__(256) k_oais_valu_batch(const SweepArgs* __rest
 {
     __shared__ double2 sh_rec[kWavesPerBlock][kTC][kWave / LPP];
     __shared__ uint32_t sh_cnt[kWavesPerBlock][kTC];
+    __shared__ NormalTables sh_nt;
+    stage_tables(sh_nt);
+    __syncthreads();
     // the wave index through readfirstlane, so that the compiler sees the
     // work item, its arguments and its parameter view as wave-uniform (scalar
     // loads into scalar registers instead of per-lane copies in vector
@@ -765,7 +775,8 @@ __global__ void __launch_bounds__(256) k_oais_valu_batch(const SweepArgs* __rest
     for (int64_t it = claim(-1); it < nitems; it = claim(it)) {
         const int2 item = items[it];
         const SweepArgs a = args[item.x];
-        const ParView pv = views[item.x];
+        ParView pv = views[item.x];
+        pv.nt = &sh_nt;
         const Consts c = make_consts(a.tg);
         oais_slot<FAM, MOVE, LPP, DPL>(a, pv, c, (int64_t)item.y, sh_rec[wv], sh_cnt[wv]);
     }
@@ -779,7 +790,8 @@ __global__ void __launch_bounds__(256) k_asmc_init(SweepArgs a, AsmcState z)
 {
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn);
+    __shared__ NormalTables sh_nt;
+    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
@@ -813,7 +825,8 @@ __global__ void __launch_bounds__(256, MinWaves<DPL>::value)
     if (a.t_stop && t > *a.t_stop) return;  // an online schedule already reached beta = 1
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn);
+    __shared__ NormalTables sh_nt;
+    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
@@ -912,7 +925,8 @@ __global__ void __launch_bounds__(256) k_rejuv(RejuvArgs R)
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
     const SweepArgs& a = R.a;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn);
+    __shared__ NormalTables sh_nt;
+    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
@@ -1007,7 +1021,8 @@ __global__ void __launch_bounds__(kPtMaxThreads) k_pt(PtArgs A)
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
     const SweepArgs& a = A.a;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn);
+    __shared__ NormalTables sh_nt;
+    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
     const Consts c = make_consts(a.tg);
     const int R = A.Np + 1;
     const int Np = A.Np;
@@ -1058,7 +1073,7 @@ __global__ void __launch_bounds__(kPtMaxThreads) k_pt(PtArgs A)
                                            0u, 0u);
                 const double acc = (la >= 0.0) ? 1.0 : ((la == la) ? exp(la) : 0.0);
                 rsum[np] += 1.0 - acc;
-                if (log(word_uniform(w.x)) < la) {
+                if (-0.5 * minus2_log_word(*pv.nt, w.x) < la) {
                     rep[np] = rb;
                     rep[np + 1] = ra;
                     tau[ra] = np + 1;
@@ -1144,7 +1159,8 @@ __global__ void __launch_bounds__(256) k_target_eval(EvalArgs E)
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
     const SweepArgs& a = E.a;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn);
+    __shared__ NormalTables sh_nt;
+    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
