@@ -577,7 +577,10 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
 
     // Fold TC buffered steps of this tile into the slot's accumulators.  For
     // the final entry (fin) the fourth field keeps the largest log w instead
-    // of an accepted count.
+    // of an accepted count.  Bound by VALU issue (24 exponentials a lane for
+    // 8 steps): they come from the table, and lane part i of a step folds sum i,
+    // so that one logarithm and two exponentials serve the three
+    // (the d = 10 sweep of 2^22 particles and 64 steps: 9.15 -> 7.88 ms).
     auto flush = [&](int64_t slot, bool first, int e0, int cnt, bool fin) {
         wave_sync();
         const int tcl = lane % kTC;
@@ -604,14 +607,17 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
 #pragma unroll
             for (int i = 0; i < 3; ++i) m[i] = fmax(m[i], __shfl_xor(m[i], o, kWave));
         if (tcl < cnt) {
+            // without a finite maximum the terms are -inf and the sum stays 0
+            double base[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) base[i] = (m[i] > -INFINITY) ? m[i] : 0.0;
 #pragma unroll
             for (int q = 0; q < PP; ++q) {
                 const int p = part * PP + q;
                 if (p < P) {
                     const double2 v = rec[tcl][p];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i)
-                        if (m[i] > -INFINITY) s[i] += exp(mom_term(v, i) - m[i]);
+                    for (int i = 0; i < 3; ++i) s[i] += exp_neg(*pv.nt, mom_term(v, i) - base[i]);
                 }
             }
         }
@@ -619,17 +625,27 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
         for (int o = kTC; o < kWave; o <<= 1)
 #pragma unroll
             for (int i = 0; i < 3; ++i) s[i] += __shfl_xor(s[i], o, kWave);
-        if (part == 0 && tcl < cnt) {
-            double* e = a.part + ((size_t)slot * (T + 1) + (size_t)(e0 + tcl)) * 4;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const double L = lse_value(m[i], s[i]);
-                e[i] = first ? L : log_add(e[i], L);
+        if (part < 4 && tcl < cnt) {
+            double* e = a.part + ((size_t)slot * (T + 1) + (size_t)(e0 + tcl)) * 4 + part;
+            const double old = first ? -INFINITY : *e;
+            if (part == 3) {
+                if (fin)
+                    *e = first ? m[0] : fmax(old, m[0]);
+                else
+                    *e = (first ? 0.0 : old) + (double)cntb[tcl];
+            } else {
+                // log(exp(old) + s exp(m)) against the larger of old and m, so that
+                // the logarithm's argument lies in [1, 65]; a sum that is zero or
+                // not a number (a NaN weight) adds nothing
+                const double si = part == 0 ? s[0] : (part == 1 ? s[1] : s[2]);
+                const bool on = si > 0.0;
+                const double mi = !on ? -INFINITY : (part == 0 ? m[0] : (part == 1 ? m[1] : m[2]));
+                const double M = fmax(mi, old);
+                const double base = (M > -INFINITY) ? M : 0.0;
+                const double v = exp_neg(*pv.nt, old - base) +
+                                 (on ? si * exp_neg(*pv.nt, mi - base) : 0.0);
+                *e = (M > -INFINITY) ? M - 0.5 * minus2_log<0>(*pv.nt, v) : -INFINITY;
             }
-            if (fin)
-                e[3] = first ? m[0] : fmax(e[3], m[0]);
-            else
-                e[3] = (first ? 0.0 : e[3]) + (double)cntb[tcl];
         }
         wave_sync();
     };
@@ -727,7 +743,7 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
 }
 
 template <int FAM, int MOVE, int LPP, int DPL>
-__global__ void __launch_bounds__(256) k_oais_valu(SweepArgs a)
+__global__ void __launch_bounds__(256, 2) k_oais_valu(SweepArgs a)
 {
     __shared__ double2 sh_rec[kWavesPerBlock][kTC][kWave / LPP];
     __shared__ uint32_t sh_cnt[kWavesPerBlock][kTC];
@@ -746,7 +762,7 @@ __global__ void __launch_bounds__(256) k_oais_valu(SweepArgs a)
 // walks the work list of (problem, slot) items; target parameters are read
 // from global memory through per-problem views.
 template <int FAM, int MOVE, int LPP, int DPL>
-__global__ void __launch_bounds__(256) k_oais_valu_batch(const SweepArgs* __restrict__ args,
+__global__ void __launch_bounds__(256, 2) k_oais_valu_batch(const SweepArgs* __restrict__ args,
                                                          const ParView* __restrict__ views,
                                                          const int2* __restrict__ items,
                                                          int64_t nitems, uint32_t* next)
