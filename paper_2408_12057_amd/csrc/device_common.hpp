@@ -158,6 +158,23 @@ __device__ __forceinline__ double group_sum(double v)
     return v;
 }
 
+// The same sum in binary32 (G <= 16).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <int G>
+__device__ __forceinline__ float group_sum32(float v)
+{
+    static_assert(G <= 16, "within a row of lanes");
+    if constexpr (G >= 2) v += dpp_f32<kDppXor1>(v);
+    if constexpr (G >= 4) v += dpp_f32<kDppXor2>(v);
+    if constexpr (G >= 8) v += dpp_f32<kDppHalfMirror>(v);
+    if constexpr (G >= 16) v += dpp_f32<kDppMirror>(v);
+    return v;
+}
+
 // Largest value of aligned groups of G lanes, by the same moves.
 template <int G>
 __device__ __forceinline__ double group_max(double v)

@@ -52,6 +52,7 @@ struct ParView {
     const double* lm;   // [DPL][LPP]
     const double* lmu;  // [K or 1][DPL][LPP]
     const NormalTables* nt;  // LDS of the workgroup (null in a stored view)
+    const float* lmf;        // mixture means, binary32 [K][LPP][DPL], or null
 };
 
 // Mixture components handled together by the particle code (the lane layout
@@ -77,10 +78,18 @@ __host__ __device__ inline size_t lane_params_offset(const TargetDev& tg)
     const int nmu = (tg.family == kGmm) ? tg.K * tg.d : tg.d;
     return (2 * kMaxK * sizeof(double) + (size_t)(tg.d + nmu) * sizeof(float) + 7) & ~(size_t)7;
 }
+// Binary32 means of a mixture whose particles span lanes, a lane's coordinates
+// contiguous (16-byte reads), behind the binary64 ones.
+__host__ __device__ inline size_t lane_param_floats(const TargetDev& tg, int lpp, int dpl)
+{
+    return (tg.family == kGmm && lpp > 1) ? (size_t)lane_means(tg) * lpp * dpl : 0;
+}
 // Dynamic LDS of a VALU kernel with the lane-layout parameters of a shape.
 __host__ __device__ inline size_t params_bytes_lanes(const TargetDev& tg, int lpp, int dpl)
 {
-    return lane_params_offset(tg) + lane_param_doubles(tg, lpp, dpl) * sizeof(double);
+    return ((lane_params_offset(tg) + 15) & ~(size_t)15) +
+           lane_param_doubles(tg, lpp, dpl) * sizeof(double) +
+           lane_param_floats(tg, lpp, dpl) * sizeof(float);
 }
 
 // Arguments of one annealing pass.

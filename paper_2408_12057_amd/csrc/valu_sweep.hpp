@@ -80,7 +80,7 @@ __device__ __forceinline__ ParView stage_params(const TargetDev& tg, char* sh)
         iv[k] = on ? 1.0 / v : 0.0;
     }
     __syncthreads();
-    return ParView{m, mu, hv, iv, nullptr, nullptr, nullptr};
+    return ParView{m, mu, hv, iv, nullptr, nullptr, nullptr, nullptr};
 }
 
 inline size_t params_bytes(const TargetDev& tg)
@@ -97,11 +97,22 @@ __device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char*
 {
     stage_tables(nt);
     const ParView base = stage_params(tg, sh);
-    double* lane = reinterpret_cast<double*>(sh + lane_params_offset(tg));
+    double* lane = reinterpret_cast<double*>(sh + ((lane_params_offset(tg) + 15) & ~(size_t)15));
     const int nl = (int)lane_param_doubles(tg, LPP, DPL);
-    for (int e = threadIdx.x; e < nl; e += blockDim.x) lane[e] = lane_param(tg, LPP, DPL, e);
+    float* lmf = nullptr;
+    if (lane_param_floats(tg, LPP, DPL) > 0) lmf = reinterpret_cast<float*>(lane + nl);
+    for (int e = threadIdx.x; e < nl; e += blockDim.x) {
+        const double v = lane_param(tg, LPP, DPL, e);
+        lane[e] = v;
+        // element (k, j, r) of the targets' means, transposed (its source is binary32)
+        const int ke = e - LPP * DPL;
+        if (lmf && ke >= 0) {
+            const int k = ke / (LPP * DPL), j = ke / LPP % DPL, r = ke % LPP;
+            lmf[(k * LPP + r) * DPL + j] = (float)v;
+        }
+    }
     __syncthreads();
-    return ParView{base.m, base.mu, base.hiv, base.iv, lane, lane + LPP * DPL, &nt};
+    return ParView{base.m, base.mu, base.hiv, base.iv, lane, lane + LPP * DPL, &nt, lmf};
 }
 
 
@@ -134,6 +145,7 @@ struct Particle {
         ParView v = pv;
         v.lm = pv.lm + z0;
         v.lmu = pv.lmu + z0;
+        if (pv.lmf) v.lmf = pv.lmf + z0;
         return v;
     }
 
@@ -145,10 +157,12 @@ struct Particle {
 
     // ell(x) = log gamma(x) - log eta(x); with GRAD also its gradient on this
     // lane's coordinates.  r = lane index inside the group.
+    // few (mixtures over several lanes): in, whether to look for the components
+    // that matter; out, whether they were at most half of them.
     template <bool GRAD>
     static __device__ __forceinline__ double eval(const TargetDev& tg, const Consts& c,
                                                   const ParView& pv0, int r, const float (&x)[DPL],
-                                                  double (&g)[DPL])
+                                                  double (&g)[DPL], bool* few = nullptr)
     {
         const ParView pv = fresh(pv0);
         if constexpr (FAM == kUnid) {
@@ -190,6 +204,9 @@ struct Particle {
             }
             sse = group_sum<LPP>(sse);
             if constexpr (LPP > 1) {
+                uint32_t near;
+                if (few && *few && (*few = near_components(tg, pv, r, x, near)))
+                    return mixture_few<GRAD>(tg, c, pv, r, x, g, sse, near);
                 return mixture_multilane<GRAD>(tg, c, pv, r, x, g, sse);
             }
             double mx = -INFINITY, s = 0.0;
@@ -204,7 +221,7 @@ struct Particle {
                 const double ek = -group_sum<LPP>(sq) * pv.hiv[k];
                 double wk;
                 if (ek > mx) {
-                    const double sc = exp(mx - ek);  // 0 on the first component
+                    const double sc = exp_neg(*pv.nt, mx - ek);  // 0 on the first component
                     s *= sc;
                     if (GRAD) {
 #pragma unroll
@@ -213,7 +230,7 @@ struct Particle {
                     mx = ek;
                     wk = 1.0;
                 } else {
-                    wk = exp(ek - mx);
+                    wk = exp_neg(*pv.nt, ek - mx);
                 }
                 s += wk;
                 if (GRAD) {
@@ -223,7 +240,7 @@ struct Particle {
                         g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
                 }
             }
-            const double lse = mx + log(s) - c.logK;
+            const double lse = mx + log_sum(*pv.nt, s) - c.logK;
             if (GRAD) {
                 const double inv_s = 1.0 / s;
 #pragma unroll
@@ -284,11 +301,11 @@ struct Particle {
         double so = 0.0;
 #pragma unroll
         for (int q = 0; q < KO; ++q) {
-            wo[q] = (q * LPP + r < K) ? exp(eo[q] - M) : 0.0;
+            wo[q] = (q * LPP + r < K) ? exp_neg(*pv.nt, eo[q] - M) : 0.0;
             so += wo[q];
         }
         const double s = group_sum<LPP>(so);
-        const double lse = M + log(s) - c.logK;
+        const double lse = M + log_sum(*pv.nt, s) - c.logK;
         if (GRAD) {
             const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
 #pragma unroll
@@ -298,6 +315,133 @@ struct Particle {
 #pragma unroll
                     for (int j = 0; j < DPL; ++j)
                         g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
+                }
+            }
+            const double inv_s = 1.0 / s;
+#pragma unroll
+            for (int j = 0; j < DPL; ++j)
+                g[j] = g[j] * inv_s + ((double)x[j] - ref(pv, r, j)) * c.inv_s2r;
+        }
+        return lse + sse * c.half_inv_s2r + c.cst_eta;
+    }
+
+    // The components whose weight relative to the largest may be above zero in
+    // binary64 (bits of `near`, the same on the particle's lanes), from distances
+    // in binary32: half the issue cycles of the binary64 ones and a third of the
+    // reduction's instructions.  States and means are binary32, so a difference is
+    // off by 2^-24 of itself and a distance, its scaling and the comparison by
+    // less than 64 such roundings (4e-6); exp underflows to zero below -746.  False
+    // when some particle of the wave has more than half the components near (or a
+    // distance is not finite: then every comparison keeps its component).
+    static __device__ __forceinline__ bool near_components(const TargetDev& tg, const ParView& pv,
+                                                           int r, const float (&x)[DPL],
+                                                           uint32_t& near)
+    {
+        constexpr int KO = (kMaxK + LPP - 1) / LPP;
+        constexpr float slack = 4e-6f;
+        const int K = tg.K;
+        float lo = -INFINITY;  // below the largest exponent
+        float hi[KO];          // above the exponents of the owned components
+#pragma unroll
+        for (int q = 0; q < KO; ++q) hi[q] = -INFINITY;
+#pragma unroll
+        for (int k0 = 0; k0 < kMaxK; k0 += kKBlock) {
+            if (k0 < K) {
+                float sq[kKBlock];
+#pragma unroll
+                for (int u = 0; u < kKBlock; ++u) {
+                    const float4* m = reinterpret_cast<const float4*>(pv.lmf + ((k0 + u) * LPP + r) * DPL);
+                    sq[u] = 0.f;
+#pragma unroll
+                    for (int jj = 0; jj < DPL / 4; ++jj) {
+                        const float4 v = m[jj];
+                        const float a = x[4 * jj] - v.x, b = x[4 * jj + 1] - v.y;
+                        const float e = x[4 * jj + 2] - v.z, f = x[4 * jj + 3] - v.w;
+                        sq[u] = fmaf(a, a, sq[u]);
+                        sq[u] = fmaf(b, b, sq[u]);
+                        sq[u] = fmaf(e, e, sq[u]);
+                        sq[u] = fmaf(f, f, sq[u]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kKBlock; ++u) {
+                    const int k = k0 + u;
+                    const float e = group_sum32<LPP>(sq[u]) * (float)pv.hiv[k];
+                    if (k < K) {
+                        lo = fmaxf(lo, -e * (1.f + slack));
+                        if ((k % LPP) == r) hi[k / LPP] = -e * (1.f - slack);
+                    }
+                }
+            }
+        }
+        const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
+        near = 0u;
+#pragma unroll
+        for (int q = 0; q < KO; ++q) {
+            const uint64_t bal = __ballot(q * LPP + r < K && !(hi[q] < lo - 746.f - slack * fabsf(lo)));
+            near |= (uint32_t)((bal >> base) & ((1u << LPP) - 1u)) << (q * LPP);
+        }
+        return __ballot(2 * __popc(near) > K) == 0;
+    }
+
+    // The mixture term from the components in `near` (bits, at least one): each
+    // particle walks its own, so a wave takes as many turns as its particle with
+    // the most.  The others' weights are exactly zero and add nothing to any sum,
+    // so the results are those of mixture_multilane bit for bit.  With the
+    // components of the d = 100, 8-component target apart (one near, mostly) an
+    // evaluation and leapfrog step issue about 200 binary64 instructions a wave
+    // instead of 496 (96 HMC steps of 20011 particles: 6.79 -> 4.82 ms).
+    template <bool GRAD>
+    static __device__ __forceinline__ double mixture_few(const TargetDev& tg, const Consts& c,
+                                                         const ParView& pv, int r,
+                                                         const float (&x)[DPL], double (&g)[DPL],
+                                                         double sse, uint32_t near)
+    {
+        constexpr int KO = (kMaxK + LPP - 1) / LPP;
+        double eo[KO];
+#pragma unroll
+        for (int q = 0; q < KO; ++q) eo[q] = -INFINITY;
+        double M = -INFINITY;
+        for (uint32_t left = near; __ballot(left != 0u) != 0; left &= left - 1u) {
+            const bool on = left != 0u;
+            const int k = on ? __ffs(left) - 1 : 0;
+            double sq = 0.0;
+#pragma unroll
+            for (int j = 0; j < DPL; ++j) {
+                const double a = (double)x[j] - mean(pv, k, r, j);
+                sq = fma(a, a, sq);
+            }
+            const double ek = -group_sum<LPP>(sq) * pv.hiv[k];
+            if (on) M = fmax(M, ek);
+#pragma unroll
+            for (int q = 0; q < KO; ++q)
+                if (on && k == q * LPP + r) eo[q] = ek;
+        }
+        const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
+        double wo[KO];
+        double so = 0.0;
+        uint32_t left = 0u;  // components with weight
+#pragma unroll
+        for (int q = 0; q < KO; ++q) {
+            wo[q] = (q * LPP + r < tg.K) ? exp_neg(*pv.nt, eo[q] - M) : 0.0;
+            so += wo[q];
+            const uint64_t bal = __ballot(!(wo[q] == 0.0));
+            left |= (uint32_t)((bal >> base) & ((1u << LPP) - 1u)) << (q * LPP);
+        }
+        const double s = group_sum<LPP>(so);
+        const double lse = M + log_sum(*pv.nt, s) - c.logK;
+        if (GRAD) {
+            for (; __ballot(left != 0u) != 0; left &= left - 1u) {
+                const bool on = left != 0u;
+                const int k = on ? __ffs(left) - 1 : 0;
+                double w = wo[0];
+#pragma unroll
+                for (int q = 1; q < KO; ++q) w = (k / LPP == q) ? wo[q] : w;
+                // (the owner's lane holds component k in the same register as here)
+                const double f = __shfl(w, base + k % LPP, kWave) * pv.iv[k];
+                if (on) {
+#pragma unroll
+                    for (int j = 0; j < DPL; ++j) g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
                 }
             }
             const double inv_s = 1.0 / s;
@@ -496,6 +640,9 @@ struct Particle {
             }
             ellp = ell;
             const double he = 0.5 * eps;
+            // the first evaluation of a trajectory looks for the components near
+            // its particles; the others do where that found few
+            bool few = pv.lmf != nullptr;
             for (int l = 0; l < L; ++l) {
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
@@ -503,7 +650,7 @@ struct Particle {
                     mom[j] += he * (-(xv - ref(pv, r, j)) * c.inv_s2r + beta * gp[j]);
                     xp[j] = (float)(xv + eps * mom[j]);
                 }
-                ellp = eval<true>(tg, c, pv, r, xp, gp);
+                ellp = eval<true>(tg, c, pv, r, xp, gp, &few);
 #pragma unroll
                 for (int j = 0; j < DPL; ++j)
                     mom[j] += he * (-((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j]);
