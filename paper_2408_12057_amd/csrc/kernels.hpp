@@ -219,7 +219,8 @@ struct ValuShape {
 };
 
 // Lanes that fill every SIMD of the GPU twice (256 CUs x 4 SIMDs x 64 x 2).
-constexpr int64_t kFillLanes = 256 * 4 * 64 * 2;
+constexpr int64_t kFillCus = 256;
+constexpr int64_t kFillLanes = kFillCus * 4 * 64 * 2;
 bool valu_shape(int d, int64_t N, ValuShape* s);
 
 // A batch of problems of one (family, move, shape) class.

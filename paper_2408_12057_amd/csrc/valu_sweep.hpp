@@ -58,7 +58,7 @@ __device__ __forceinline__ Consts make_consts(const TargetDev& tg)
 
 // Target parameters staged in LDS: reference mean [d], then the Gaussian mean
 // [d] or the mixture means [K*d], then the mixture 1/(2 v_k), 1/v_k (the view
-// type ParView is declared in kernels.hpp).
+// type ParView is declared in kernels.hpp); the caller's barrier publishes them.
 
 __device__ __forceinline__ ParView stage_params(const TargetDev& tg, char* sh)
 {
@@ -79,7 +79,6 @@ __device__ __forceinline__ ParView stage_params(const TargetDev& tg, char* sh)
         hv[k] = on ? 0.5 / v : 0.0;
         iv[k] = on ? 1.0 / v : 0.0;
     }
-    __syncthreads();
     return ParView{m, mu, hv, iv, nullptr, nullptr, nullptr, nullptr};
 }
 
@@ -274,27 +273,27 @@ struct Particle {
         // interleave; the lane layout and 1/(2 v_k) are zero-padded to whole
         // blocks and a padded component gets e_k = -inf (weight 0)
         double M = -INFINITY;
+#pragma unroll 1
+        for (int k0 = 0; k0 < K; k0 += kKBlock) {
+            double sq[kKBlock];
 #pragma unroll
-        for (int k0 = 0; k0 < kMaxK; k0 += kKBlock) {
-            if (k0 < K) {
-                double sq[kKBlock];
+            for (int u = 0; u < kKBlock; ++u) {
+                sq[u] = 0.0;
 #pragma unroll
-                for (int u = 0; u < kKBlock; ++u) {
-                    sq[u] = 0.0;
-#pragma unroll
-                    for (int j = 0; j < DPL; ++j) {
-                        const double a = (double)x[j] - mean(pv, k0 + u, r, j);
-                        sq[u] = fma(a, a, sq[u]);
-                    }
+                for (int j = 0; j < DPL; ++j) {
+                    const double a = (double)x[j] - mean(pv, k0 + u, r, j);
+                    sq[u] = fma(a, a, sq[u]);
                 }
+            }
 #pragma unroll
-                for (int u = 0; u < kKBlock; ++u) {
-                    const int k = k0 + u;
-                    double ek = -group_sum<LPP>(sq[u]) * pv.hiv[k];
-                    if (k >= K) ek = -INFINITY;
-                    M = fmax(M, ek);
-                    if ((k % LPP) == r) eo[k / LPP] = ek;
-                }
+            for (int u = 0; u < kKBlock; ++u) {
+                const int k = k0 + u;
+                double ek = -group_sum<LPP>(sq[u]) * pv.hiv[k];
+                if (k >= K) ek = -INFINITY;
+                M = fmax(M, ek);
+#pragma unroll
+                for (int q = 0; q < KO; ++q)
+                    if (k == q * LPP + r) eo[q] = ek;
             }
         }
         double wo[KO];
@@ -308,14 +307,15 @@ struct Particle {
         const double lse = M + log_sum(*pv.nt, s) - c.logK;
         if (GRAD) {
             const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
+#pragma unroll 1
+            for (int k = 0; k < K; ++k) {
+                double w = wo[0];
 #pragma unroll
-            for (int k = 0; k < kMaxK; ++k) {
-                if (k < K) {
-                    const double f = __shfl(wo[k / LPP], base + k % LPP, kWave) * pv.iv[k];
+                for (int q = 1; q < KO; ++q) w = (k / LPP == q) ? wo[q] : w;
+                const double f = __shfl(w, base + k % LPP, kWave) * pv.iv[k];
 #pragma unroll
-                    for (int j = 0; j < DPL; ++j)
-                        g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
-                }
+                for (int j = 0; j < DPL; ++j)
+                    g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
             }
             const double inv_s = 1.0 / s;
 #pragma unroll
@@ -344,34 +344,32 @@ struct Particle {
         float hi[KO];          // above the exponents of the owned components
 #pragma unroll
         for (int q = 0; q < KO; ++q) hi[q] = -INFINITY;
+#pragma unroll 1
+        for (int k0 = 0; k0 < K; k0 += kKBlock) {
+            float sq[kKBlock];
 #pragma unroll
-        for (int k0 = 0; k0 < kMaxK; k0 += kKBlock) {
-            if (k0 < K) {
-                float sq[kKBlock];
+            for (int u = 0; u < kKBlock; ++u) {
+                const float4* m = reinterpret_cast<const float4*>(pv.lmf + ((k0 + u) * LPP + r) * DPL);
+                sq[u] = 0.f;
 #pragma unroll
-                for (int u = 0; u < kKBlock; ++u) {
-                    const float4* m = reinterpret_cast<const float4*>(pv.lmf + ((k0 + u) * LPP + r) * DPL);
-                    sq[u] = 0.f;
-#pragma unroll
-                    for (int jj = 0; jj < DPL / 4; ++jj) {
-                        const float4 v = m[jj];
-                        const float a = x[4 * jj] - v.x, b = x[4 * jj + 1] - v.y;
-                        const float e = x[4 * jj + 2] - v.z, f = x[4 * jj + 3] - v.w;
-                        sq[u] = fmaf(a, a, sq[u]);
-                        sq[u] = fmaf(b, b, sq[u]);
-                        sq[u] = fmaf(e, e, sq[u]);
-                        sq[u] = fmaf(f, f, sq[u]);
-                    }
+                for (int jj = 0; jj < DPL / 4; ++jj) {
+                    const float4 v = m[jj];
+                    const float a = x[4 * jj] - v.x, b = x[4 * jj + 1] - v.y;
+                    const float e = x[4 * jj + 2] - v.z, f = x[4 * jj + 3] - v.w;
+                    sq[u] = fmaf(a, a, sq[u]);
+                    sq[u] = fmaf(b, b, sq[u]);
+                    sq[u] = fmaf(e, e, sq[u]);
+                    sq[u] = fmaf(f, f, sq[u]);
                 }
+            }
 #pragma unroll
-                for (int u = 0; u < kKBlock; ++u) {
-                    const int k = k0 + u;
-                    const float e = group_sum32<LPP>(sq[u]) * (float)pv.hiv[k];
-                    if (k < K) {
-                        lo = fmaxf(lo, -e * (1.f + slack));
-                        if ((k % LPP) == r) hi[k / LPP] = -e * (1.f - slack);
-                    }
-                }
+            for (int u = 0; u < kKBlock; ++u) {
+                const int k = k0 + u;
+                const float e = group_sum32<LPP>(sq[u]) * (float)pv.hiv[k];
+                lo = (k < K) ? fmaxf(lo, -e * (1.f + slack)) : lo;
+#pragma unroll
+                for (int q = 0; q < KO; ++q)
+                    if (k == q * LPP + r) hi[q] = -e * (1.f - slack);
             }
         }
         const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
@@ -688,14 +686,21 @@ constexpr int kWavesPerBlock = 4;
 
 // Minimum waves per SIMD requested from the compiler for the resampling
 // variant's step kernel: four for particles with at most 8 coordinates per
-// lane (the 128-register budget costs some spills and buys latency hiding:
-// for the mixture/HMC step 5% faster than three waves and 30% faster than
-// two), the compiler's choice otherwise (wider lanes would spill heavily).
-// The AIS sweeps, which keep more state across their time loop, measured
-// slower with such a request.
-template <int DPL>
+// lane, three for the mixture/HMC step (the d = 100, 8-component step at N = 65536:
+// 164.6 us on two waves, 137 us on three, 219.6 us on four, whose 128-register
+// budget spills inside the trajectory), the compiler's choice for wider lanes
+// (which would spill heavily).
+template <int FAM, int MOVE, int DPL>
 struct MinWaves {
-    static constexpr int value = DPL <= 8 ? 4 : 1;
+    static constexpr int value = DPL > 8 ? 1 : (FAM == kGmm && uses_grad(MOVE)) ? 3 : 4;
+};
+
+// The AIS sweeps' slots give the chip at most two waves per SIMD: lanes of up to
+// 12 coordinates are kept within the registers of two, wider ones (which would
+// spill) are the compiler's choice.
+template <int DPL>
+struct SweepWaves {
+    static constexpr int value = DPL <= 12 ? 2 : 1;
 };
 
 // log of w_{t-1} (g_t)^i for a record v = (log w_{t-1}, log g_t): g^0 = 1 also
@@ -890,7 +895,7 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
 }
 
 template <int FAM, int MOVE, int LPP, int DPL>
-__global__ void __launch_bounds__(256, 2) k_oais_valu(SweepArgs a)
+__global__ void __launch_bounds__(256, (SweepWaves<DPL>::value)) k_oais_valu(SweepArgs a)
 {
     __shared__ double2 sh_rec[kWavesPerBlock][kTC][kWave / LPP];
     __shared__ uint32_t sh_cnt[kWavesPerBlock][kTC];
@@ -909,7 +914,7 @@ __global__ void __launch_bounds__(256, 2) k_oais_valu(SweepArgs a)
 // walks the work list of (problem, slot) items; target parameters are read
 // from global memory through per-problem views.
 template <int FAM, int MOVE, int LPP, int DPL>
-__global__ void __launch_bounds__(256, 2) k_oais_valu_batch(const SweepArgs* __restrict__ args,
+__global__ void __launch_bounds__(256, (SweepWaves<DPL>::value)) k_oais_valu_batch(const SweepArgs* __restrict__ args,
                                                          const ParView* __restrict__ views,
                                                          const int2* __restrict__ items,
                                                          int64_t nitems, uint32_t* next)
@@ -981,8 +986,84 @@ __global__ void __launch_bounds__(256) k_asmc_init(SweepArgs a, AsmcState z)
     }
 }
 
+// A lane's coordinates r DPL .. of particle row `row` of an [N][d] array, zero
+// beyond d: in quads where d is a multiple of four (rows then start on 16 bytes and
+// a quad lies within d or beyond it), one by one otherwise.
+template <int DPL>
+__device__ __forceinline__ void load_row(const float* __restrict__ p, int64_t row, int d, int r,
+                                         float (&x)[DPL])
+{
+    const float* q = p + (size_t)row * d + r * DPL;
+    if (d % 4 == 0) {
+#pragma unroll
+        for (int j = 0; j < DPL; j += 4) {
+            const float4 v = (r * DPL + j < d) ? *reinterpret_cast<const float4*>(q + j)
+                                               : make_float4(0.f, 0.f, 0.f, 0.f);
+            x[j] = v.x;
+            x[j + 1] = v.y;
+            x[j + 2] = v.z;
+            x[j + 3] = v.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) x[j] = (r * DPL + j < d) ? q[j] : 0.f;
+    }
+}
+template <int DPL>
+__device__ __forceinline__ void load_row(const double* __restrict__ p, int64_t row, int d, int r,
+                                         double (&x)[DPL])
+{
+    const double* q = p + (size_t)row * d + r * DPL;
+    if (d % 4 == 0) {
+#pragma unroll
+        for (int j = 0; j < DPL; j += 2) {
+            const double2 v = (r * DPL + j < d) ? *reinterpret_cast<const double2*>(q + j)
+                                                : make_double2(0.0, 0.0);
+            x[j] = v.x;
+            x[j + 1] = v.y;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) x[j] = (r * DPL + j < d) ? q[j] : 0.0;
+    }
+}
+template <int DPL>
+__device__ __forceinline__ void store_row(float* __restrict__ p, int64_t row, int d, int r,
+                                          const float (&x)[DPL])
+{
+    float* q = p + (size_t)row * d + r * DPL;
+    if (d % 4 == 0) {
+#pragma unroll
+        for (int j = 0; j < DPL; j += 4)
+            if (r * DPL + j < d)
+                *reinterpret_cast<float4*>(q + j) = make_float4(x[j], x[j + 1], x[j + 2], x[j + 3]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < DPL; ++j)
+            if (r * DPL + j < d) q[j] = x[j];
+    }
+}
+template <int DPL>
+__device__ __forceinline__ void store_row(double* __restrict__ p, int64_t row, int d, int r,
+                                          const double (&x)[DPL])
+{
+    double* q = p + (size_t)row * d + r * DPL;
+    if (d % 4 == 0) {
+#pragma unroll
+        for (int j = 0; j < DPL; j += 2)
+            if (r * DPL + j < d) *reinterpret_cast<double2*>(q + j) = make_double2(x[j], x[j + 1]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < DPL; ++j)
+            if (r * DPL + j < d) q[j] = x[j];
+    }
+}
+
+// The launch has at most as many blocks as are resident, and each walks over
+// tiles: the staging of the target's parameters and tables (a few us of dependent
+// loads) is paid once a block and not once a tile (the step above: 195 -> 142 us).
 template <int FAM, int MOVE, int LPP, int DPL>
-__global__ void __launch_bounds__(256, MinWaves<DPL>::value)
+__global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
     k_asmc_step(SweepArgs a, AsmcState z, int t)
 {
     if (a.t_stop && t > *a.t_stop) return;  // an online schedule already reached beta = 1
@@ -993,13 +1074,8 @@ __global__ void __launch_bounds__(256, MinWaves<DPL>::value)
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
-    const int64_t tile =
-        (int64_t)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    if (tile >= a.ntiles) return;  // whole wave leaves together
-    const int64_t n64 = tile * P + pl;
-    const bool valid = n64 < a.N;
     const int d = a.tg.d;
-    const int64_t nl = valid ? n64 : a.N - 1;  // invalid lanes work on a copy, write nothing
+    const double beta = a.beta[t], dbeta = beta - a.beta[t - 1], eps = a.eps[t - 1];
     // state, ell and (MALA, HMC) grad ell as the previous step left them:
     // after a resampling event at the previous step (its flag is still set:
     // the merge of this step has not run) the gathered copies X2, G2, ell2
@@ -1008,67 +1084,84 @@ __global__ void __launch_bounds__(256, MinWaves<DPL>::value)
     const bool rs = z.X2 != nullptr && z.scal[2] != 0.0;
     const float* Xs = rs ? z.X2 : z.X;
     const double* Gs = rs ? z.G2 : z.G;
-    float x[DPL];
-    double g[DPL];
+    const double* es = rs ? z.ell2 : z.ell;
+    for (int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock +
+                        __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+         tile < a.ntiles; tile += (int64_t)gridDim.x * kWavesPerBlock) {
+        const int64_t n64 = tile * P + pl;
+        const bool valid = n64 < a.N;
+        const int64_t nl = valid ? n64 : a.N - 1;  // invalid lanes work on a copy, write nothing
+        float x[DPL];
+        double g[DPL];
+        load_row<DPL>(Xs, nl, d, r, x);
+        if constexpr (uses_grad(MOVE)) {
+            load_row<DPL>(Gs, nl, d, r, g);
+        } else {
 #pragma unroll
-    for (int j = 0; j < DPL; ++j) {
-        const int i = r * DPL + j;
-        x[j] = (i < d) ? Xs[(size_t)nl * d + i] : 0.f;
-        g[j] = (uses_grad(MOVE) && i < d) ? Gs[(size_t)nl * d + i] : 0.0;
-    }
-    double ell = rs ? z.ell2[nl] : z.ell[nl];
-    double lw = rs ? 0.0 : z.lw[nl];
-    const double lg = (a.beta[t] - a.beta[t - 1]) * ell;
-    // tile statistics: lse of lw, lw+lg, lw+2lg, 2(lw+lg) over the tile's
-    // particles: the maximum by an xor butterfly over the particle groups
-    // (every lane ends with the same value), then one exponential per lane
-    // against it and a butterfly sum
-    double m[4], s[4];
-    {
-        const double v[4] = {lw, lw + lg, lw + 2.0 * lg, 2.0 * (lw + lg)};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = valid ? v[i] : -INFINITY;
-#pragma unroll
-        for (int o = LPP; o < kWave; o <<= 1)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) m[i] = fmax(m[i], __shfl_xor(m[i], o, kWave));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s[i] = (valid && m[i] > -INFINITY) ? exp(v[i] - m[i]) : 0.0;
-#pragma unroll
-        for (int o = LPP; o < kWave; o <<= 1)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] += __shfl_xor(s[i], o, kWave);
-    }
-    lw += lg;
-    const bool acc = Particle<FAM, LPP, DPL>::template move<MOVE>(
-        a.tg, c, pv, a.key, (uint32_t)nl, (uint32_t)t, r, a.leapfrog, a.beta[t], a.eps[t - 1], x,
-        ell, g);
-    const uint64_t bal = __ballot(valid && acc && r == 0);
-    if (lane == 0) {
-        double* tp = z.tile_part + (size_t)tile * 8;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tp[i] = lse_value(m[i], s[i]);
-        tp[4] = m[1];  // max of log w_{t^-}
-        tp[5] = (double)__popcll(bal);
-    }
-    if (valid) {
-#pragma unroll
-        for (int j = 0; j < DPL; ++j) {
-            const int i = r * DPL + j;
-            if (i < d) {
-                z.X[(size_t)n64 * d + i] = x[j];
-                if (uses_grad(MOVE)) z.G[(size_t)n64 * d + i] = g[j];
-            }
+            for (int j = 0; j < DPL; ++j) g[j] = 0.0;
         }
-        if (r == 0) {
-            z.ell[n64] = ell;
-            z.lw[n64] = lw;
-            uint32_t w = z.accw[n64] | ((acc ? 1u : 0u) << ((t - 1) & 31));
-            if (((t - 1) & 31) == 31 || t == a.T) {
-                if (a.acc_bits) a.acc_bits[(size_t)n64 * a.acc_words + (t - 1) / 32] = w;
-                w = 0u;
+        double ell = es[nl];
+        double lw = rs ? 0.0 : z.lw[nl];
+        const double lg = dbeta * ell;
+        // tile statistics: lse of lw, lw+lg, lw+2lg, 2(lw+lg) over the tile's
+        // particles: the maximum by an xor butterfly over the particle groups
+        // (every lane ends with the same value), then the exponentials against
+        // it and a butterfly sum.  Where a particle spans four lanes or more, its
+        // lane i mod 4 forms statistic i (a quarter of the instructions).
+        constexpr int NS = LPP >= 4 ? 1 : 4;
+        double m[NS], s[NS];
+        {
+            const double v4[4] = {lw, lw + lg, lw + 2.0 * lg, 2.0 * (lw + lg)};
+            double v[NS];
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                if constexpr (NS == 4)
+                    v[i] = v4[i];
+                else
+                    v[i] = (r & 2) ? ((r & 1) ? v4[3] : v4[2]) : ((r & 1) ? v4[1] : v4[0]);
+                m[i] = valid ? v[i] : -INFINITY;
             }
-            z.accw[n64] = w;
+#pragma unroll
+            for (int o = LPP; o < kWave; o <<= 1)
+#pragma unroll
+                for (int i = 0; i < NS; ++i) m[i] = fmax(m[i], __shfl_xor(m[i], o, kWave));
+#pragma unroll
+            for (int i = 0; i < NS; ++i)
+                s[i] = (valid && m[i] > -INFINITY) ? exp_neg(*pv.nt, v[i] - m[i]) : 0.0;
+#pragma unroll
+            for (int o = LPP; o < kWave; o <<= 1)
+#pragma unroll
+                for (int i = 0; i < NS; ++i) s[i] += __shfl_xor(s[i], o, kWave);
+        }
+        lw += lg;
+        const bool acc = Particle<FAM, LPP, DPL>::template move<MOVE>(
+            a.tg, c, pv, a.key, (uint32_t)nl, (uint32_t)t, r, a.leapfrog, beta, eps, x, ell, g);
+        const uint64_t bal = __ballot(valid && acc && r == 0);
+        if (lane < 4) {
+            // lane i records statistic i (a sum that is not positive: nothing finite)
+            double mi = m[0], si = s[0];
+            if constexpr (NS == 4) {
+                mi = (lane & 2) ? ((lane & 1) ? m[3] : m[2]) : ((lane & 1) ? m[1] : m[0]);
+                si = (lane & 2) ? ((lane & 1) ? s[3] : s[2]) : ((lane & 1) ? s[1] : s[0]);
+            }
+            double* tp = z.tile_part + (size_t)tile * 8;
+            tp[lane] = (si > 0.0) ? mi + log_sum(*pv.nt, si) : -INFINITY;
+            if (lane == 1) tp[4] = mi;  // max of log w_{t^-}
+            if (lane == 0) tp[5] = (double)__popcll(bal);
+        }
+        if (valid) {
+            store_row<DPL>(z.X, n64, d, r, x);
+            if constexpr (uses_grad(MOVE)) store_row<DPL>(z.G, n64, d, r, g);
+            if (r == 0) {
+                z.ell[n64] = ell;
+                z.lw[n64] = lw;
+                uint32_t w = z.accw[n64] | ((acc ? 1u : 0u) << ((t - 1) & 31));
+                if (((t - 1) & 31) == 31 || t == a.T) {
+                    if (a.acc_bits) a.acc_bits[(size_t)n64 * a.acc_words + (t - 1) / 32] = w;
+                    w = 0u;
+                }
+                z.accw[n64] = w;
+            }
         }
     }
 }
@@ -1408,7 +1501,15 @@ struct Launch {
     }
     static hipError_t step(const SweepArgs& a, const AsmcState& z, int t, hipStream_t st)
     {
-        const int64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
+        // resident blocks of this instantiation (a property of the kernel)
+        static const int per_cu = [] {
+            int n = 0;
+            const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &n, reinterpret_cast<const void*>(&k_asmc_step<FAM, MOVE, LPP, DPL>), 256, 0);
+            return (e == hipSuccess && n > 0) ? n : 2;
+        }();
+        const int64_t blocks = std::min<int64_t>((a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock,
+                                                 (int64_t)kFillCus * per_cu);
         hipLaunchKernelGGL((k_asmc_step<FAM, MOVE, LPP, DPL>), dim3((unsigned)blocks), dim3(256),
                            params_bytes_lanes(a.tg, LPP, DPL), st, a, z, t);
         return hipGetLastError();
