@@ -205,36 +205,75 @@ __device__ __forceinline__ void put_slice(float (*stc)[kSt], const Slice& t)
     dst[4] = t.v4; dst[5] = t.v5; dst[6] = t.v6; dst[7] = t.v7;
 }
 
-// Feature tiles of the gradient product: the packed halves (features
-// [0, KH) in columns 0 .. KH - 1, [KH, 2 KH) in columns 32 .. 32 + KH - 1)
-// take one 32-column tile each, or, for KH <= 16, share one tile whose
-// column j reads packed column col_of(j, KH) (feature j): half the gradient
-// instructions for d <= 32.
+// Feature tiles of the gradient product G += sigma(-u)^T X'.
+//
+// Bound by the matrix instructions (every FP32 shape has the same nominal rate),
+// so what counts is the columns multiplied that are no feature.  Whole tiles of 32
+// features take the accumulator of the logits as it stands (v_mfma_f32_32x32x2);
+// the rest takes a chunk's rows one by one as operands with a lane per particle
+// (v_permlane32_swap of the two particle groups' registers leaves row
+// slot_row(q, 0) of all 64 particles in one and row slot_row(q, 1) in the other)
+// and tiles of 16 features (v_mfma_f32_16x16x1_4b, the same features for its four
+// blocks of particles) or 4 (v_mfma_f32_4x4x1_16b, a lane's four results its
+// particle's).  Measured cycles a row of 64 particles: 64.2 for 32 features, 33.9
+// for 16, 9.7 for 4, and 4.5 for the swaps where there is a rest; so a rest of 24
+// (58 cycles and more LDS reads) takes a 32-tile.  A tile's lane reads the packed
+// columns of its features, wherever they stand.  A round at n = 10000, d = 50,
+// N = 16384: 64.0 -> 60.7 ms (two tiles of 32 before, 64 columns for 50 features);
+// at n = 5000 a sweep gains 1.28 at d <= 8, 1.12 at 16, 1.17 at 37.
+// Every shape adds its products one after the other with one rounding each, so the
+// sums are those of a chain over the rows in the order (q, 0), (q, 1), whatever
+// the tiles (the results keep their bits).
 template <int KH>
 struct GradTiles {
-    static constexpr int nft = KH <= 16 ? 1 : 2;
+    static constexpr int rest = 2 * KH % 32;
+    static constexpr int n32 = 2 * KH / 32 + (rest > 20 ? 1 : 0);
+    static constexpr int n16 = (rest >= 16 && rest <= 20) ? 1 : 0;
+    static constexpr int n4 = rest > 20 ? 0 : (rest % 16 + 3) / 4;
+    static constexpr int nr = n16 + n4;               // tiles of the rest
+    static constexpr int nk = 8 * n32 + 4 * n16 + n4;  // float4 of accumulators a lane
 };
 
-// The 32 NFT gradient accumulators of a lane as 8 NFT float4 (element 4 k + i
-// is G[g][ft][q] with (g * NFT + ft) * 16 + q = 4 k + i), stored
-// lane-interleaved (float4 k of lane l at k * 64 + l) so every 128-bit LDS
-// access is conflict-free.
-template <int NFT>
-__device__ __forceinline__ void store_grad(floatx4* dst, const floatx16 (&G)[2][NFT], int l)
+// The accumulators of the whole tiles: G[g][ft][q] is feature 32 ft + j of particle
+// 32 g + slot_row(q, h); of the rest: element 4 b + i of g16 is feature
+// 32 n32 + 4 (l / 16) + i of particle 16 b + l % 16, element i of g4[t] feature
+// 32 n32 + 16 n16 + 4 t + i of particle l.
+template <int KH>
+struct RestAcc {
+    floatx16 g16;
+    floatx4 g4[GradTiles<KH>::n4 > 0 ? GradTiles<KH>::n4 : 1];
+};
+
+// The accumulators as float4 (element 4 k + i of the whole tiles is G[g][ft][q] with
+// (g n32 + ft) 16 + q = 4 k + i, then those of the rest), stored lane-interleaved
+// (float4 k of lane l at k * 64 + l) so every 128-bit LDS access is conflict-free.
+template <int KH, int NFT>
+__device__ __forceinline__ void store_grad(floatx4* dst, const floatx16 (&G)[2][NFT], const RestAcc<KH>& Re,
+                                           int l)
 {
+    using Ti = GradTiles<KH>;
 #pragma unroll
-    for (int k = 0; k < 8 * NFT; ++k) {
+    for (int k = 0; k < 8 * Ti::n32; ++k) {
         const floatx16& v = G[k / (4 * NFT)][(k / 4) % NFT];
         const int q = 4 * (k % 4);
         dst[k * kWave + l] = floatx4{v[q], v[q + 1], v[q + 2], v[q + 3]};
     }
+    dst += 8 * Ti::n32 * kWave;
+    if constexpr (Ti::n16 > 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            dst[k * kWave + l] = floatx4{Re.g16[4 * k], Re.g16[4 * k + 1], Re.g16[4 * k + 2], Re.g16[4 * k + 3]};
+    }
+#pragma unroll
+    for (int t = 0; t < Ti::n4; ++t) dst[(4 * Ti::n16 + t) * kWave + l] = Re.g4[t];
 }
 
-template <int NFT>
-__device__ __forceinline__ void add_grad(floatx16 (&G)[2][NFT], const floatx4* src, int l)
+template <int KH, int NFT>
+__device__ __forceinline__ void add_grad(floatx16 (&G)[2][NFT], RestAcc<KH>& Re, const floatx4* src, int l)
 {
+    using Ti = GradTiles<KH>;
 #pragma unroll
-    for (int k = 0; k < 8 * NFT; ++k) {
+    for (int k = 0; k < 8 * Ti::n32; ++k) {
         floatx16& v = G[k / (4 * NFT)][(k / 4) % NFT];
         const int q = 4 * (k % 4);
         const floatx4 u = src[k * kWave + l];
@@ -243,6 +282,25 @@ __device__ __forceinline__ void add_grad(floatx16 (&G)[2][NFT], const floatx4* s
         v[q + 2] += u[2];
         v[q + 3] += u[3];
     }
+    src += 8 * Ti::n32 * kWave;
+    if constexpr (Ti::n16 > 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const floatx4 u = src[k * kWave + l];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Re.g16[4 * k + i] += u[i];
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < Ti::n4; ++t) Re.g4[t] += src[(4 * Ti::n16 + t) * kWave + l];
+}
+
+// a = [a low half, b low half], b = [a high half, b high half].
+__device__ __forceinline__ void swap_halves(float& a, float& b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
 }
 
 // ell and grad ell at sh.prop for the 64 particles of the tile; results in
@@ -256,22 +314,35 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
 {
     constexpr int kLWaves = LCfg::waves;
     constexpr double kLn2 = 0.693147180559945309;
-    constexpr int NFT = GradTiles<KH>::nft;
+    using Ti = GradTiles<KH>;
+    constexpr int N32 = Ti::n32, N16 = Ti::n16, NR = Ti::nr, NK = Ti::nk;
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform
     const int l = tid % kWave;
     const int h = l / 32;
     const int j = l % 32;
-    // packed column of this lane's gradient column in each feature tile
-    const int cb0 = (NFT == 1) ? col_of(j, KH) : j;
+    // packed column of this lane's feature in each feature tile
+    int col32[N32 > 0 ? N32 : 1], col[NR > 0 ? NR : 1];
+#pragma unroll
+    for (int ft = 0; ft < N32; ++ft) col32[ft] = col_of(32 * ft + j, KH);
+#pragma unroll
+    for (int c = 0; c < NR; ++c)
+        col[c] = col_of(32 * N32 + (c < N16 ? l % 16 : 16 * N16 + 4 * (c - N16) + l % 4), KH);
 
-    floatx16 G[2][NFT];
+    floatx16 G[2][N32 > 0 ? N32 : 1];
 #pragma unroll
     for (int g = 0; g < 2; ++g)
 #pragma unroll
-        for (int ft = 0; ft < NFT; ++ft)
+        for (int ft = 0; ft < N32; ++ft)
 #pragma unroll
             for (int q = 0; q < 16; ++q) G[g][ft][q] = 0.f;
+    RestAcc<KH> Re;
+    if constexpr (N16 > 0) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) Re.g16[q] = 0.f;
+    }
+#pragma unroll
+    for (int t = 0; t < Ti::n4; ++t) Re.g4[t] = floatx4{0.f, 0.f, 0.f, 0.f};
     double llacc[2] = {0.0, 0.0};
 
     const int nchunks = wave_rows(n_pad) / kRows;
@@ -301,16 +372,15 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
                 acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, sh.prop[32 * g + j][32 * h + s],
                                                             acc[g], 0, 0, 0);
         }
-        // row slots: the epilogue of slot q + 1 is issued between the four
-        // gradient products of slot q (G[g][ft] += sigma(-u_g)^T X'_ft over
-        // its rows)
+        // row slots: the epilogue of slot q + 1 is issued between the gradient
+        // products of slot q's two rows
         float lin[2] = {0.f, 0.f}, prod[2] = {1.f, 1.f};
         EpiTmp t0, t1;
         epi_a(acc[0][0], t0);
         acc[0][0] = epi_b(acc[0][0], t0, lin[0], prod[0]);
         epi_a(acc[1][0], t1);
         acc[1][0] = epi_b(acc[1][0], t1, lin[1], prod[1]);
-        if constexpr (NFT == 2) {
+        if constexpr (NR == 0 && N32 == 2) {
             float bx0 = stc[slot_row(0, h)][j], bx1 = stc[slot_row(0, h)][32 + j];
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
@@ -323,25 +393,25 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
                 G[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(acc[1][q], bx0, G[1][0], 0, 0, 0);
                 if (q < 15) acc[0][qn] = epi_b(acc[0][qn], t0, lin[0], prod[0]);
                 __builtin_amdgcn_sched_barrier(0);
-                G[0][NFT - 1] =
-                    __builtin_amdgcn_mfma_f32_32x32x2f32(acc[0][q], bx1, G[0][NFT - 1], 0, 0, 0);
+                G[0][1] =
+                    __builtin_amdgcn_mfma_f32_32x32x2f32(acc[0][q], bx1, G[0][1], 0, 0, 0);
                 if (q < 15) epi_a(acc[1][qn], t1);
                 __builtin_amdgcn_sched_barrier(0);
-                G[1][NFT - 1] =
-                    __builtin_amdgcn_mfma_f32_32x32x2f32(acc[1][q], bx1, G[1][NFT - 1], 0, 0, 0);
+                G[1][1] =
+                    __builtin_amdgcn_mfma_f32_32x32x2f32(acc[1][q], bx1, G[1][1], 0, 0, 0);
                 if (q < 15) acc[1][qn] = epi_b(acc[1][qn], t1, lin[1], prod[1]);
                 __builtin_amdgcn_sched_barrier(0);
                 bx0 = nbx0;
                 bx1 = nbx1;
             }
-        } else {
+        } else if constexpr (NR == 0) {
             // one feature tile: the two halves of each slot's epilogue go
             // between its two gradient products
-            float bx = stc[slot_row(0, h)][cb0];
+            float bx = stc[slot_row(0, h)][col32[0]];
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
                 const int qn = (q < 15) ? q + 1 : 15;
-                const float nbx = stc[slot_row(qn, h)][cb0];
+                const float nbx = stc[slot_row(qn, h)][col32[0]];
                 G[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(acc[0][q], bx, G[0][0], 0, 0, 0);
                 if (q < 15) {
                     epi_a(acc[0][qn], t0);
@@ -355,6 +425,62 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 bx = nbx;
+            }
+        } else {
+            // whole tiles, then the rest's rows: a half of the next slot's epilogue
+            // after each of the first four products
+            constexpr int M32 = N32 > 0 ? N32 : 1;
+            float bx[M32], xr[2][NR];
+#pragma unroll
+            for (int ft = 0; ft < N32; ++ft) bx[ft] = stc[slot_row(0, h)][col32[ft]];
+#pragma unroll
+            for (int c = 0; c < NR; ++c) {
+                xr[0][c] = stc[slot_row(0, 0)][col[c]];
+                xr[1][c] = stc[slot_row(0, 1)][col[c]];
+            }
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int qn = (q < 15) ? q + 1 : 15;
+                float nbx[M32], nxr[2][NR];
+#pragma unroll
+                for (int ft = 0; ft < N32; ++ft) nbx[ft] = stc[slot_row(qn, h)][col32[ft]];
+#pragma unroll
+                for (int c = 0; c < NR; ++c) {
+                    nxr[0][c] = stc[slot_row(qn, 0)][col[c]];
+                    nxr[1][c] = stc[slot_row(qn, 1)][col[c]];
+                }
+                float row0 = acc[0][q], row1 = acc[1][q];
+#pragma unroll
+                for (int p = 0; p < 2 * N32 + 2 * NR; ++p) {
+                    if (p < 2 * N32) {
+                        G[p % 2][p / 2] = __builtin_amdgcn_mfma_f32_32x32x2f32(acc[p % 2][q], bx[p / 2],
+                                                                             G[p % 2][p / 2], 0, 0, 0);
+                    } else {
+                        const int hh = (p - 2 * N32) / NR, c = (p - 2 * N32) % NR;
+                        if (p == 2 * N32) swap_halves(row0, row1);
+                        const float rv = hh == 0 ? row0 : row1;
+                        if (c < N16)
+                            Re.g16 = __builtin_amdgcn_mfma_f32_16x16x1f32(xr[hh][c], rv, Re.g16, 0, 0, 0);
+                        else
+                            Re.g4[c - N16] =
+                                __builtin_amdgcn_mfma_f32_4x4x1f32(xr[hh][c], rv, Re.g4[c - N16], 0, 0, 0);
+                    }
+                    if (q < 15) {
+                        if (p == 0) epi_a(acc[0][qn], t0);
+                        if (p == 1) acc[0][qn] = epi_b(acc[0][qn], t0, lin[0], prod[0]);
+                        if (p == (NR == 1 && N32 == 0 ? 0 : 2)) epi_a(acc[1][qn], t1);
+                        if (p == (NR == 1 && N32 == 0 ? 1 : 3))
+                            acc[1][qn] = epi_b(acc[1][qn], t1, lin[1], prod[1]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int ft = 0; ft < N32; ++ft) bx[ft] = nbx[ft];
+#pragma unroll
+                for (int c = 0; c < NR; ++c) {
+                    xr[0][c] = nxr[0][c];
+                    xr[1][c] = nxr[1][c];
+                }
             }
         }
         // the chunk's data rows: the sum of min(u, 0) plus the log of the
@@ -381,8 +507,8 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
     // gradient: G_w + G_{w+4} on waves 0..3, then wave 0 adds waves 1, 2, 3
     // in that order (fixed tree), through four 16 KB slots of the staging area
     floatx4* red = reinterpret_cast<floatx4*>(&sh.stage[0][0][0]);
-    constexpr int kSlot = 8 * NFT * kWave;  // float4 per slot
-    if (w >= 4) store_grad(red + (w - 4) * kSlot, G, l);
+    constexpr int kSlot = NK * kWave;  // float4 per slot
+    if (w >= 4) store_grad<KH>(red + (w - 4) * kSlot, G, Re, l);
     if (tid < kLP) {
         double s = 0.0;
         for (int ww = 0; ww < kLWaves; ++ww) s += sh.llpart[ww][tid];
@@ -390,15 +516,14 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
     }
     lsync();
     if (w < 4) {
-        add_grad(G, red + w * kSlot, l);
-        store_grad(red + w * kSlot, G, l);  // slot w is read only by wave w
+        add_grad<KH>(G, Re, red + w * kSlot, l);
+        store_grad<KH>(red + w * kSlot, G, Re, l);  // slot w is read only by wave w
     }
     lsync();
-    // ((slot 0 + slot 1) + slot 2) + slot 3: wave w sums float4 NFT w ..
-    // NFT w + NFT - 1 of every lane and writes those gradient entries
-#pragma unroll
-    for (int kk = 0; kk < NFT; ++kk) {
-        const int k = NFT * w + kk;
+    // ((slot 0 + slot 1) + slot 2) + slot 3: wave w sums float4 N32 w ..
+    // N32 w + N32 - 1 of every lane, and float4 8 N32 + w and on of the rest, and
+    // writes those gradient entries
+    auto total = [&](int k) {
         floatx4 v = red[k * kWave + l];
 #pragma unroll
         for (int sl = 1; sl < 4; ++sl) {
@@ -408,11 +533,24 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
             v[2] += u[2];
             v[3] += u[3];
         }
-        // float4 k holds G[g][ft][q .. q + 3], (g * NFT + ft) * 16 + q = 4 k
-        const int g = k / (4 * NFT), ft = (k / 4) % NFT, q0 = 4 * (k % 4);
-        const int col = (NFT == 1) ? cb0 : 32 * ft + j;
+        return v;
+    };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sh.glp[32 * g + slot_row(q0 + i, h)][col] = v[i];
+    for (int kk = 0; kk < N32; ++kk) {
+        const int k = N32 * w + kk;
+        const floatx4 v = total(k);
+        const int g = k / (4 * N32), ft = k / 4 % N32, q0 = 4 * (k % 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sh.glp[32 * g + slot_row(q0 + i, h)][col_of(32 * ft + j, KH)] = v[i];
+    }
+    if (w < NK - 8 * N32) {
+        static_assert(NK - 8 * N32 <= kLWaves, "one float4 of the rest a wave");
+        const floatx4 v = total(8 * N32 + w);
+        const bool wide = w < 4 * N16;
+        const int p = wide ? 16 * w + l % 16 : l;
+        const int f0 = 32 * N32 + (wide ? 4 * (l / 16) : 16 * N16 + 4 * (w - 4 * N16));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sh.glp[p][col_of(f0 + i, KH)] = v[i];
     }
     // chunk 0 of the next evaluation (the rows do not change between steps)
     first = fetch_slice(Xp, n_pad, 0);
