@@ -220,7 +220,7 @@ struct Particle {
                 const double ek = -group_sum<LPP>(sq) * pv.hiv[k];
                 double wk;
                 if (ek > mx) {
-                    const double sc = exp_neg(*pv.nt, mx - ek);  // 0 on the first component
+                    const double sc = exp(mx - ek);  // 0 on the first component
                     s *= sc;
                     if (GRAD) {
 #pragma unroll
@@ -229,7 +229,7 @@ struct Particle {
                     mx = ek;
                     wk = 1.0;
                 } else {
-                    wk = exp_neg(*pv.nt, ek - mx);
+                    wk = exp(ek - mx);
                 }
                 s += wk;
                 if (GRAD) {
@@ -239,7 +239,7 @@ struct Particle {
                         g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
                 }
             }
-            const double lse = mx + log_sum(*pv.nt, s) - c.logK;
+            const double lse = mx + log(s) - c.logK;
             if (GRAD) {
                 const double inv_s = 1.0 / s;
 #pragma unroll
@@ -300,11 +300,11 @@ struct Particle {
         double so = 0.0;
 #pragma unroll
         for (int q = 0; q < KO; ++q) {
-            wo[q] = (q * LPP + r < K) ? exp_neg(*pv.nt, eo[q] - M) : 0.0;
+            wo[q] = (q * LPP + r < K) ? exp(eo[q] - M) : 0.0;
             so += wo[q];
         }
         const double s = group_sum<LPP>(so);
-        const double lse = M + log_sum(*pv.nt, s) - c.logK;
+        const double lse = M + log(s) - c.logK;
         if (GRAD) {
             const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
 #pragma unroll 1
@@ -388,7 +388,7 @@ struct Particle {
     // so the results are those of mixture_multilane bit for bit.  With the
     // components of the d = 100, 8-component target apart (one near, mostly) an
     // evaluation and leapfrog step issue about 200 binary64 instructions a wave
-    // instead of 496 (96 HMC steps of 20011 particles: 6.79 -> 4.82 ms).
+    // instead of 496 (96 HMC steps of 20011 particles: 6.20 -> 4.48 ms).
     template <bool GRAD>
     static __device__ __forceinline__ double mixture_few(const TargetDev& tg, const Consts& c,
                                                          const ParView& pv, int r,
@@ -396,6 +396,31 @@ struct Particle {
                                                          double sse, uint32_t near)
     {
         constexpr int KO = (kMaxK + LPP - 1) / LPP;
+        if (__ballot((near & (near - 1u)) != 0u) == 0) {
+            // one component a particle: its weight, their sum and its inverse are
+            // 1, the logarithm 0 (exactly, as the functions give them).  The
+            // exponent and the inverse stand behind an empty asm, so that no
+            // product is fused here that the general form rounds.
+            const int k = __ffs(near) - 1;
+            double sq = 0.0, inv_s = 1.0;
+#pragma unroll
+            for (int j = 0; j < DPL; ++j) {
+                const double a = (double)x[j] - mean(pv, k, r, j);
+                sq = fma(a, a, sq);
+            }
+            double ek = -group_sum<LPP>(sq) * pv.hiv[k];
+            asm volatile("" : "+v"(ek), "+v"(inv_s));
+            const double lse = ek - c.logK;
+            if (GRAD) {
+                const double f = pv.iv[k];
+#pragma unroll
+                for (int j = 0; j < DPL; ++j) {
+                    g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
+                    g[j] = g[j] * inv_s + ((double)x[j] - ref(pv, r, j)) * c.inv_s2r;
+                }
+            }
+            return lse + sse * c.half_inv_s2r + c.cst_eta;
+        }
         double eo[KO];
 #pragma unroll
         for (int q = 0; q < KO; ++q) eo[q] = -INFINITY;
@@ -421,13 +446,13 @@ struct Particle {
         uint32_t left = 0u;  // components with weight
 #pragma unroll
         for (int q = 0; q < KO; ++q) {
-            wo[q] = (q * LPP + r < tg.K) ? exp_neg(*pv.nt, eo[q] - M) : 0.0;
+            wo[q] = (q * LPP + r < tg.K) ? exp(eo[q] - M) : 0.0;
             so += wo[q];
             const uint64_t bal = __ballot(!(wo[q] == 0.0));
             left |= (uint32_t)((bal >> base) & ((1u << LPP) - 1u)) << (q * LPP);
         }
         const double s = group_sum<LPP>(so);
-        const double lse = M + log_sum(*pv.nt, s) - c.logK;
+        const double lse = M + log(s) - c.logK;
         if (GRAD) {
             for (; __ballot(left != 0u) != 0; left &= left - 1u) {
                 const bool on = left != 0u;
@@ -468,7 +493,7 @@ struct Particle {
         for (int u = 0; u < 4; ++u) q[u] = 0.0;
         // (one lane per particle: every block but the last holds coordinates in a
         // shape that fits d, and a branch around it would only keep the blocks from
-        // interleaving; 2^22 particles at d = 10, 64 steps: 7.87 -> 7.69 ms)
+        // interleaving; 2^22 particles at d = 10, 64 steps: 0.18 ms of 8)
         const bool last = bb == DPL / 4 - 1;
         if ((LPP == 1 && !last) || 4 * b < d) {
             double z[4];
@@ -733,10 +758,12 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
 
     // Fold TC buffered steps of this tile into the slot's accumulators.  For
     // the final entry (fin) the fourth field keeps the largest log w instead
-    // of an accepted count.  Bound by VALU issue (24 exponentials a lane for
-    // 8 steps): they come from the table, and lane part i of a step folds sum i,
-    // so that one logarithm and two exponentials serve the three
-    // (the d = 10 sweep of 2^22 particles and 64 steps: 9.15 -> 7.88 ms).
+    // of an accepted count.  Bound by VALU issue: the 24 exponentials a lane for 8
+    // steps run without branches, and lane part i of a step folds sum i, so that one
+    // logarithm and one log_add serve the three (2^22 particles at d = 10,
+    // 64 steps: 9.15 -> 8.0 ms).  The functions and
+    // their order stay those of one lane after the other: where one particle holds
+    // all the weight the discrepancy L_2 - 2 L_1 + L_0 is what their roundings leave.
     auto flush = [&](int64_t slot, bool first, int e0, int cnt, bool fin) {
         wave_sync();
         const int tcl = lane % kTC;
@@ -773,7 +800,7 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
                 if (p < P) {
                     const double2 v = rec[tcl][p];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) s[i] += exp_neg(*pv.nt, mom_term(v, i) - base[i]);
+                    for (int i = 0; i < 3; ++i) s[i] += exp(mom_term(v, i) - base[i]);
                 }
             }
         }
@@ -790,17 +817,10 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
                 else
                     *e = (first ? 0.0 : old) + (double)cntb[tcl];
             } else {
-                // log(exp(old) + s exp(m)) against the larger of old and m, so that
-                // the logarithm's argument lies in [1, 65]; a sum that is zero or
-                // not a number (a NaN weight) adds nothing
-                const double si = part == 0 ? s[0] : (part == 1 ? s[1] : s[2]);
-                const bool on = si > 0.0;
-                const double mi = !on ? -INFINITY : (part == 0 ? m[0] : (part == 1 ? m[1] : m[2]));
-                const double M = fmax(mi, old);
-                const double base = (M > -INFINITY) ? M : 0.0;
-                const double v = exp_neg(*pv.nt, old - base) +
-                                 (on ? si * exp_neg(*pv.nt, mi - base) : 0.0);
-                *e = (M > -INFINITY) ? M - 0.5 * minus2_log<0>(*pv.nt, v) : -INFINITY;
+                // (a sum that is zero or not a number, of a NaN weight, adds nothing)
+                const double L = lse_value(part == 0 ? m[0] : (part == 1 ? m[1] : m[2]),
+                                           part == 0 ? s[0] : (part == 1 ? s[1] : s[2]));
+                *e = first ? L : log_add(old, L);
             }
         }
         wave_sync();
@@ -1131,7 +1151,7 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
                 for (int i = 0; i < NS; ++i) m[i] = fmax(m[i], __shfl_xor(m[i], o, kWave));
 #pragma unroll
             for (int i = 0; i < NS; ++i)
-                s[i] = (valid && m[i] > -INFINITY) ? exp_neg(*pv.nt, v[i] - m[i]) : 0.0;
+                s[i] = (valid && m[i] > -INFINITY) ? exp(v[i] - m[i]) : 0.0;
 #pragma unroll
             for (int o = LPP; o < kWave; o <<= 1)
 #pragma unroll
@@ -1142,14 +1162,14 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
             a.tg, c, pv, a.key, (uint32_t)nl, (uint32_t)t, r, a.leapfrog, beta, eps, x, ell, g);
         const uint64_t bal = __ballot(valid && acc && r == 0);
         if (lane < 4) {
-            // lane i records statistic i (a sum that is not positive: nothing finite)
+            // lane i records statistic i
             double mi = m[0], si = s[0];
             if constexpr (NS == 4) {
                 mi = (lane & 2) ? ((lane & 1) ? m[3] : m[2]) : ((lane & 1) ? m[1] : m[0]);
                 si = (lane & 2) ? ((lane & 1) ? s[3] : s[2]) : ((lane & 1) ? s[1] : s[0]);
             }
             double* tp = z.tile_part + (size_t)tile * 8;
-            tp[lane] = (si > 0.0) ? mi + log_sum(*pv.nt, si) : -INFINITY;
+            tp[lane] = lse_value(mi, si);
             if (lane == 1) tp[4] = mi;  // max of log w_{t^-}
             if (lane == 0) tp[5] = (double)__popcll(bal);
         }
