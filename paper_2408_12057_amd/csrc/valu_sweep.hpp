@@ -605,11 +605,35 @@ struct Particle {
             }
             return any;
         }
-        double z[DPL];
-        if constexpr (uses_grad(MOVE)) normals(pv, key, n, t, kStreamMove, r, tg.d, z);
         float xp[DPL];
         double gp[DPL];
         double ellp;
+        const bool acc = propose<MOVE>(tg, c, pv, key, n, t, r, L, beta, eps, x, ell, g, xp, ellp, gp,
+                                       forced);
+        if (acc) {
+#pragma unroll
+            for (int j = 0; j < DPL; ++j) {
+                x[j] = xp[j];
+                if (uses_grad(MOVE)) g[j] = gp[j];
+            }
+            ell = ellp;
+        }
+        return acc;
+    }
+
+    // The proposal of one step and its accept decision, the state as it was: what
+    // becomes of both is the caller's (grad ell of a state that lies in memory is
+    // dead here after the first half step).
+    template <int MOVE>
+    static __device__ __forceinline__ bool propose(const TargetDev& tg, const Consts& c,
+                                                   const ParView& pv, const RngKey& key, uint32_t n,
+                                                   uint32_t t, int r, int L, double beta, double eps,
+                                                   const float (&x)[DPL], double ell,
+                                                   const double (&g)[DPL], float (&xp)[DPL],
+                                                   double& ellp, double (&gp)[DPL], int forced = -1)
+    {
+        double z[DPL];
+        if constexpr (uses_grad(MOVE)) normals(pv, key, n, t, kStreamMove, r, tg.d, z);
         double log_alpha;
         if constexpr (MOVE == kRwmh) {
             double dle = 0.0;
@@ -694,16 +718,7 @@ struct Particle {
                         group_sum<LPP>(kin1) + group_sum<LPP>(kin0);
         }
         const uint4 w = draw_block(key, n, t, kStreamAccept, 0u, 0u);
-        const bool acc = (forced >= 0) ? (forced != 0) : (-0.5 * minus2_log_word(*pv.nt, w.x) < log_alpha);
-        if (acc) {
-#pragma unroll
-            for (int j = 0; j < DPL; ++j) {
-                x[j] = xp[j];
-                if (uses_grad(MOVE)) g[j] = gp[j];
-            }
-            ell = ellp;
-        }
-        return acc;
+        return (forced >= 0) ? (forced != 0) : (-0.5 * minus2_log_word(*pv.nt, w.x) < log_alpha);
     }
 };
 
@@ -714,14 +729,19 @@ constexpr int kTC = 8;      // steps buffered before a transposed reduction
 constexpr int kWavesPerBlock = 4;
 
 // Minimum waves per SIMD requested from the compiler for the resampling
-// variant's step kernel: four for particles with at most 8 coordinates per
-// lane, three for the mixture/HMC step (the d = 100, 8-component step at N = 65536:
-// 164.6 us on two waves, 137 us on three, 219.6 us on four, whose 128-register
-// budget spills inside the trajectory), the compiler's choice for wider lanes
-// (which would spill heavily).
+// variant's step kernel: four where a lane holds 4 coordinates or a step needs no
+// gradients of a mixture, three for HMC with 8 (the d = 100, 8-component
+// step at N = 65536: 150 us on two waves, 126 us on three, over 200 on
+// four, whose 128-register budget spills inside the trajectory), two for MALA on
+// mixtures with 8 (d = 100, 8 components, 40 steps of N = 30000: 2.59 ms, on three
+// 2.68), the compiler's choice for wider lanes (which would spill heavily).
 template <int FAM, int MOVE, int DPL>
 struct MinWaves {
-    static constexpr int value = DPL > 8 ? 1 : (FAM == kGmm && uses_grad(MOVE)) ? 3 : 4;
+    static constexpr int value = DPL > 8                        ? 1
+                                 : DPL <= 4                     ? 4
+                                 : MOVE == kHmc                 ? 3
+                                 : FAM == kGmm && MOVE == kMala ? 2
+                                                                : 4;
 };
 
 // The AIS sweeps' slots give the chip at most two waves per SIMD: lanes of up to
@@ -1158,9 +1178,6 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
                 for (int i = 0; i < NS; ++i) s[i] += __shfl_xor(s[i], o, kWave);
         }
         lw += lg;
-        const bool acc = Particle<FAM, LPP, DPL>::template move<MOVE>(
-            a.tg, c, pv, a.key, (uint32_t)nl, (uint32_t)t, r, a.leapfrog, beta, eps, x, ell, g);
-        const uint64_t bal = __ballot(valid && acc && r == 0);
         if (lane < 4) {
             // lane i records statistic i
             double mi = m[0], si = s[0];
@@ -1171,11 +1188,35 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
             double* tp = z.tile_part + (size_t)tile * 8;
             tp[lane] = lse_value(mi, si);
             if (lane == 1) tp[4] = mi;  // max of log w_{t^-}
-            if (lane == 0) tp[5] = (double)__popcll(bal);
         }
+        bool acc;
+        if constexpr (uses_grad(MOVE)) {
+            // a rejected proposal's state is still in memory: neither it nor its
+            // gradient is held over the step, and it is written only where it
+            // comes from the gathered copies
+            float xp[DPL];
+            double gp[DPL], ellp;
+            acc = Particle<FAM, LPP, DPL>::template propose<MOVE>(a.tg, c, pv, a.key, (uint32_t)nl,
+                                                                  (uint32_t)t, r, a.leapfrog, beta, eps,
+                                                                  x, ell, g, xp, ellp, gp);
+            if (acc) ell = ellp;
+            if (rs && !acc) {
+                load_row<DPL>(Xs, nl, d, r, xp);
+                load_row<DPL>(Gs, nl, d, r, gp);
+            }
+            if (valid && (rs || acc)) {
+                store_row<DPL>(z.X, n64, d, r, xp);
+                store_row<DPL>(z.G, n64, d, r, gp);
+            }
+        } else {
+            acc = Particle<FAM, LPP, DPL>::template move<MOVE>(a.tg, c, pv, a.key, (uint32_t)nl,
+                                                               (uint32_t)t, r, a.leapfrog, beta, eps, x,
+                                                               ell, g);
+            if (valid && (rs || acc)) store_row<DPL>(z.X, n64, d, r, x);
+        }
+        const uint64_t bal = __ballot(valid && acc && r == 0);
+        if (lane == 0) z.tile_part[(size_t)tile * 8 + 5] = (double)__popcll(bal);
         if (valid) {
-            store_row<DPL>(z.X, n64, d, r, x);
-            if constexpr (uses_grad(MOVE)) store_row<DPL>(z.G, n64, d, r, g);
             if (r == 0) {
                 z.ell[n64] = ell;
                 z.lw[n64] = lw;
