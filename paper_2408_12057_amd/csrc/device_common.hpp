@@ -140,6 +140,9 @@ constexpr int kDppXor1 = 0xB1;
 constexpr int kDppXor2 = 0x4E;
 constexpr int kDppHalfMirror = 0x141;
 constexpr int kDppMirror = 0x140;
+constexpr int kDppQuadRev = 0x1B;  // lane ^ 3
+constexpr int kDppRor4 = 0x124;    // lane - 4 mod 16
+constexpr int kDppRor8 = 0x128;    // lane ^ 8
 
 // Sum over aligned groups of G lanes (G a power of two <= 64).  All lanes of a
 // group end with the same bits: each level adds the partial sums of two
@@ -158,21 +161,11 @@ __device__ __forceinline__ double group_sum(double v)
     return v;
 }
 
-// The same sum in binary32 (G <= 16).
+// The value of another lane of the row, in binary32.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v)
 {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-template <int G>
-__device__ __forceinline__ float group_sum32(float v)
-{
-    static_assert(G <= 16, "within a row of lanes");
-    if constexpr (G >= 2) v += dpp_f32<kDppXor1>(v);
-    if constexpr (G >= 4) v += dpp_f32<kDppXor2>(v);
-    if constexpr (G >= 8) v += dpp_f32<kDppHalfMirror>(v);
-    if constexpr (G >= 16) v += dpp_f32<kDppMirror>(v);
-    return v;
 }
 
 // Largest value of aligned groups of G lanes, by the same moves.

@@ -158,10 +158,14 @@ struct Particle {
     // lane's coordinates.  r = lane index inside the group.
     // few (mixtures over several lanes): in, whether to look for the components
     // that matter; out, whether they were at most half of them.
+    // value: whether ell itself is wanted (else 0 comes back: within a trajectory
+    // only the gradient is, and the sums over the lanes and the logarithm are not
+    // formed).
     template <bool GRAD>
     static __device__ __forceinline__ double eval(const TargetDev& tg, const Consts& c,
                                                   const ParView& pv0, int r, const float (&x)[DPL],
-                                                  double (&g)[DPL], bool* few = nullptr)
+                                                  double (&g)[DPL], bool* few = nullptr,
+                                                  bool value = true)
     {
         const ParView pv = fresh(pv0);
         if constexpr (FAM == kUnid) {
@@ -180,6 +184,16 @@ struct Particle {
             return k * log1p((u - p) / p) + (n - k) * log1p(-(u - p) / (1.0 - p));
         } else if constexpr (FAM == kGauss) {
             double ssg = 0.0, sse = 0.0;
+            if (GRAD && !value) {
+#pragma unroll
+                for (int j = 0; j < DPL; ++j) {
+                    const double xv = (double)x[j];
+                    const double a = xv - mean(pv, 0, r, j);
+                    const double b = xv - ref(pv, r, j);
+                    g[j] = -a * c.inv_s2 + b * c.inv_s2r;
+                }
+                return 0.0;
+            }
 #pragma unroll
             for (int j = 0; j < DPL; ++j) {
                 const double xv = (double)x[j];
@@ -196,17 +210,21 @@ struct Particle {
             // over k with a running maximum (log-sum-exp and responsibilities)
             double sse = 0.0;
 #pragma unroll
-            for (int j = 0; j < DPL; ++j) {
-                const double b = (double)x[j] - ref(pv, r, j);
-                sse = fma(b, b, sse);
+            for (int j = 0; j < DPL; ++j)
                 if (GRAD) g[j] = 0.0;
+            if (value) {
+#pragma unroll
+                for (int j = 0; j < DPL; ++j) {
+                    const double b = (double)x[j] - ref(pv, r, j);
+                    sse = fma(b, b, sse);
+                }
+                sse = group_sum<LPP>(sse);
             }
-            sse = group_sum<LPP>(sse);
             if constexpr (LPP > 1) {
                 uint32_t near;
                 if (few && *few && (*few = near_components(tg, pv, r, x, near)))
-                    return mixture_few<GRAD>(tg, c, pv, r, x, g, sse, near);
-                return mixture_multilane<GRAD>(tg, c, pv, r, x, g, sse);
+                    return mixture_few<GRAD>(tg, c, pv, r, x, g, sse, near, value);
+                return mixture_multilane<GRAD>(tg, c, pv, r, x, g, sse, value);
             }
             double mx = -INFINITY, s = 0.0;
 #pragma unroll 1
@@ -239,7 +257,7 @@ struct Particle {
                         g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
                 }
             }
-            const double lse = mx + log(s) - c.logK;
+            const double lse = value ? mx + log(s) - c.logK : 0.0;
             if (GRAD) {
                 const double inv_s = 1.0 / s;
 #pragma unroll
@@ -261,7 +279,8 @@ struct Particle {
     static __device__ __forceinline__ double mixture_multilane(const TargetDev& tg, const Consts& c,
                                                                const ParView& pv, int r,
                                                                const float (&x)[DPL],
-                                                               double (&g)[DPL], double sse)
+                                                               double (&g)[DPL], double sse,
+                                                               bool value)
     {
         constexpr int KO = (kMaxK + LPP - 1) / LPP;  // components owned by a lane
         const int K = tg.K;
@@ -304,7 +323,7 @@ struct Particle {
             so += wo[q];
         }
         const double s = group_sum<LPP>(so);
-        const double lse = M + log(s) - c.logK;
+        const double lse = value ? M + log(s) - c.logK : 0.0;
         if (GRAD) {
             const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
 #pragma unroll 1
@@ -327,8 +346,9 @@ struct Particle {
 
     // The components whose weight relative to the largest may be above zero in
     // binary64 (bits of `near`, the same on the particle's lanes), from distances
-    // in binary32: half the issue cycles of the binary64 ones and a third of the
-    // reduction's instructions.  States and means are binary32, so a difference is
+    // in binary32: half the issue cycles of the binary64 ones, and sums over the lanes
+    // that leave each lane its own components (13 instructions for four, against 32
+    // for sums that every lane holds, and the comparison is made once).  States and means are binary32, so a difference is
     // off by 2^-24 of itself and a distance, its scaling and the comparison by
     // less than 64 such roundings (4e-6); exp underflows to zero below -746.  False
     // when some particle of the wave has more than half the components near (or a
@@ -338,6 +358,8 @@ struct Particle {
                                                            uint32_t& near)
     {
         constexpr int KO = (kMaxK + LPP - 1) / LPP;
+        constexpr int C = LPP >= 4 ? 4 : 2;
+        static_assert(kKBlock == 4, "two levels of the exchange");
         constexpr float slack = 4e-6f;
         const int K = tg.K;
         float lo = -INFINITY;  // below the largest exponent
@@ -362,16 +384,35 @@ struct Particle {
                     sq[u] = fmaf(f, f, sq[u]);
                 }
             }
+            // sums over the lanes that leave component k0 + r mod C (and those C,
+            // 2 C, .. behind it) with lane r
 #pragma unroll
-            for (int u = 0; u < kKBlock; ++u) {
-                const int k = k0 + u;
-                const float e = group_sum32<LPP>(sq[u]) * (float)pv.hiv[k];
+            for (int v = 0; v < kKBlock / 2; ++v)
+                sq[v] = ((r & 1) ? sq[2 * v + 1] : sq[2 * v]) +
+                        dpp_f32<kDppXor1>((r & 1) ? sq[2 * v] : sq[2 * v + 1]);
+            if constexpr (C == 4) {
+#pragma unroll
+                for (int v = 0; v < kKBlock / 4; ++v)
+                    sq[v] = ((r & 2) ? sq[2 * v + 1] : sq[2 * v]) +
+                            dpp_f32<kDppXor2>((r & 2) ? sq[2 * v] : sq[2 * v + 1]);
+            }
+#pragma unroll
+            for (int v = 0; v < kKBlock / C; ++v) {
+                const int k = k0 + C * v + (r & (C - 1));
+                if constexpr (LPP == 8) sq[v] += dpp_f32<kDppHalfMirror>(dpp_f32<kDppQuadRev>(sq[v]));
+                if constexpr (LPP == 16) {
+                    sq[v] += dpp_f32<kDppRor8>(sq[v]);
+                    sq[v] += dpp_f32<kDppRor4>(sq[v]);
+                }
+                const float e = sq[v] * (float)pv.hiv[k];
                 lo = (k < K) ? fmaxf(lo, -e * (1.f + slack)) : lo;
 #pragma unroll
                 for (int q = 0; q < KO; ++q)
                     if (k == q * LPP + r) hi[q] = -e * (1.f - slack);
             }
         }
+        lo = fmaxf(lo, dpp_f32<kDppXor1>(lo));
+        if constexpr (C == 4) lo = fmaxf(lo, dpp_f32<kDppXor2>(lo));
         const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
         near = 0u;
 #pragma unroll
@@ -387,13 +428,15 @@ struct Particle {
     // the most.  The others' weights are exactly zero and add nothing to any sum,
     // so the results are those of mixture_multilane bit for bit.  With the
     // components of the d = 100, 8-component target apart (one near, mostly) an
-    // evaluation and leapfrog step issue about 200 binary64 instructions a wave
-    // instead of 496 (96 HMC steps of 20011 particles: 6.20 -> 4.48 ms).
+    // evaluation and leapfrog step issue about 115 binary64 instructions a wave
+    // instead of 496 (96 HMC steps of 20011 particles: 6.20 -> 3.93 ms, of which
+    // 4.44 -> 3.93 come from ell formed at a trajectory's end only, one force an
+    // evaluation and the reduction of near_components).
     template <bool GRAD>
     static __device__ __forceinline__ double mixture_few(const TargetDev& tg, const Consts& c,
                                                          const ParView& pv, int r,
                                                          const float (&x)[DPL], double (&g)[DPL],
-                                                         double sse, uint32_t near)
+                                                         double sse, uint32_t near, bool value)
     {
         constexpr int KO = (kMaxK + LPP - 1) / LPP;
         if (__ballot((near & (near - 1u)) != 0u) == 0) {
@@ -402,15 +445,19 @@ struct Particle {
             // exponent and the inverse stand behind an empty asm, so that no
             // product is fused here that the general form rounds.
             const int k = __ffs(near) - 1;
-            double sq = 0.0, inv_s = 1.0;
+            double lse = 0.0, inv_s = 1.0;
+            asm volatile("" : "+v"(inv_s));
+            if (value) {
+                double sq = 0.0;
 #pragma unroll
-            for (int j = 0; j < DPL; ++j) {
-                const double a = (double)x[j] - mean(pv, k, r, j);
-                sq = fma(a, a, sq);
+                for (int j = 0; j < DPL; ++j) {
+                    const double a = (double)x[j] - mean(pv, k, r, j);
+                    sq = fma(a, a, sq);
+                }
+                double ek = -group_sum<LPP>(sq) * pv.hiv[k];
+                asm volatile("" : "+v"(ek));
+                lse = ek - c.logK;
             }
-            double ek = -group_sum<LPP>(sq) * pv.hiv[k];
-            asm volatile("" : "+v"(ek), "+v"(inv_s));
-            const double lse = ek - c.logK;
             if (GRAD) {
                 const double f = pv.iv[k];
 #pragma unroll
@@ -452,7 +499,7 @@ struct Particle {
             left |= (uint32_t)((bal >> base) & ((1u << LPP) - 1u)) << (q * LPP);
         }
         const double s = group_sum<LPP>(so);
-        const double lse = M + log(s) - c.logK;
+        const double lse = value ? M + log(s) - c.logK : 0.0;
         if (GRAD) {
             for (; __ballot(left != 0u) != 0; left &= left - 1u) {
                 const bool on = left != 0u;
@@ -691,20 +738,26 @@ struct Particle {
             }
             ellp = ell;
             const double he = 0.5 * eps;
+            // the force at the end of a leapfrog step is the next one's at its start
+            double force[DPL];
+#pragma unroll
+            for (int j = 0; j < DPL; ++j)
+                force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
             // the first evaluation of a trajectory looks for the components near
             // its particles; the others do where that found few
             bool few = pv.lmf != nullptr;
             for (int l = 0; l < L; ++l) {
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
-                    const double xv = (double)xp[j];
-                    mom[j] += he * (-(xv - ref(pv, r, j)) * c.inv_s2r + beta * gp[j]);
-                    xp[j] = (float)(xv + eps * mom[j]);
+                    mom[j] += he * force[j];
+                    xp[j] = (float)((double)xp[j] + eps * mom[j]);
                 }
-                ellp = eval<true>(tg, c, pv, r, xp, gp, &few);
+                ellp = eval<true>(tg, c, pv, r, xp, gp, &few, l + 1 == L);
 #pragma unroll
-                for (int j = 0; j < DPL; ++j)
-                    mom[j] += he * (-((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j]);
+                for (int j = 0; j < DPL; ++j) {
+                    force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
+                    mom[j] += he * force[j];
+                }
             }
             double kin1 = 0.0, dle = 0.0;
 #pragma unroll
