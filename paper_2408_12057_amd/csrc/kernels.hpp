@@ -276,6 +276,7 @@ __host__ __device__ inline size_t pt_shared_bytes(const PtArgs& A, int lpp, int 
     return off + R * sizeof(double) + (size_t)A.Np * sizeof(double) + 3 * R * sizeof(int) +
            16 * sizeof(double);
 }
+hipError_t launch_pt_reduce(const PtArgs& A, const ValuShape& s, double* res, hipStream_t st);
 hipError_t launch_rejuv_reduce(const double* tsum, int64_t ntiles, int d, double samples,
                                double* out, hipStream_t st);
 // Systematic resampling of lw[N] for the event word of step t (particle word

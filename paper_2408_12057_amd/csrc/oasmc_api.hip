@@ -123,7 +123,7 @@ enum BufId {
     B_BETA, B_EPS, B_PART, B_LOGG, B_ACC, B_SCAL, B_X, B_X2, B_ELL, B_ELL2, B_LW, B_ACCW,
     B_TPART, B_NRES, B_ESS, B_RES, B_C, B_BTOT, B_LWO, B_XO, B_LOGREG, B_CKPT, B_SEG, B_ABITS,
     B_GPART, B_GRAD, B_DEVRUN, B_DEVDESC, B_G, B_G2, B_BLK, B_RJ_ANC, B_RJ_SUM, B_RJ_OUT,
-    B_RJ_LW, B_RJ_X, B_ZSTOP, B_PT_OUT, B_PT_F, B_COUNT
+    B_RJ_LW, B_RJ_X, B_ZSTOP, B_PT_OUT, B_PT_F, B_PT_RES, B_COUNT
 };
 
 template <typename T>
@@ -1336,7 +1336,9 @@ int oasmc_pt(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel* 
     A.stride = 3 * (int64_t)Np + 2;
     if (pt_shared_bytes(A, shape.lpp, shape.dpl) > h->lds_per_block)
         return fail(OASMC_EUNSUPPORTED, "too many chains for the LDS of one workgroup");
-    double *dbeta, *deps, *out, *fpart;
+    double *dbeta, *deps, *out, *fpart, *dres;
+    const int nres = 2 * Np + 1 + 2 * d;
+    HIP_TRY(wget(h, B_PT_RES, (size_t)nres, &dres));
     HIP_TRY(wget(h, B_BETA, (size_t)R, &dbeta));
     HIP_TRY(wget(h, B_EPS, (size_t)R, &deps));
     HIP_TRY(wget(h, B_PT_OUT, (size_t)K * A.stride, &out));
@@ -1350,9 +1352,9 @@ int oasmc_pt(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel* 
     if (h->prof) HIP_TRY(hipEventRecord(h->ev0, st));
     HIP_TRY(launch_pt(A, shape, st));
     if (h->prof) HIP_TRY(hipEventRecord(h->ev1, st));
-    std::vector<double> ho((size_t)K * A.stride), hf((size_t)K * 16 * 2 * d);
-    HIP_TRY(hipMemcpyAsync(ho.data(), out, sizeof(double) * ho.size(), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(hf.data(), fpart, sizeof(double) * hf.size(), hipMemcpyDeviceToHost, st));
+    HIP_TRY(launch_pt_reduce(A, shape, dres, st));
+    std::vector<double> res((size_t)nres);
+    HIP_TRY(hipMemcpyAsync(res.data(), dres, sizeof(double) * res.size(), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (h->prof) {
         float ms = 0.f;
@@ -1361,48 +1363,18 @@ int oasmc_pt(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel* 
         h->prof_launches += 1;
         h->prof_steps += (double)K * R * Tp;
     }
-    // the copies' outputs in copy order: stepping stones pooled over the K T'
-    // terms of each temperature, rejections averaged over the proposals
     double lz = 0.0;
-    const double lkt = std::log((double)K * Tp);
     for (int n = 0; n < Np; ++n) {
-        double m = -INFINITY, sum = 0.0;
-        for (int k = 0; k < K; ++k) {
-            const double mk = ho[(size_t)k * A.stride + 2 * n], sk = ho[(size_t)k * A.stride + 2 * n + 1];
-            if (!(mk > -INFINITY) || !(sk > 0.0)) continue;
-            if (mk > m) {
-                sum = sum * std::exp(m - mk) + sk;
-                m = mk;
-            } else {
-                sum += sk * std::exp(mk - m);
-            }
-        }
-        const double v = (sum > 0.0) ? m + std::log(sum) - lkt : -INFINITY;
-        if (ss) ss[n] = v;
-        lz += v;
+        if (ss) ss[n] = res[n];
+        lz += res[n];
         // pair n is proposed at the iterations t of its parity
         const double cnt = (double)K * ((n % 2 == 0) ? (Tp / 2) : ((Tp + 1) / 2));
-        double rs = 0.0;
-        for (int k = 0; k < K; ++k) rs += ho[(size_t)k * A.stride + 2 * Np + n];
-        if (rej) rej[n] = cnt > 0 ? rs / cnt : NAN;
+        if (rej) rej[n] = cnt > 0 ? res[Np + n] / cnt : NAN;
     }
-    if (trips) {
-        double tr = 0.0;
-        for (int k = 0; k < K; ++k) tr += ho[(size_t)k * A.stride + 3 * Np];
-        *trips = (int64_t)std::llround(tr);
-    }
+    if (trips) *trips = (int64_t)std::llround(res[2 * Np]);
     if (tmean && tsecond) {
-        const int waves = (R + P - 1) / P;
-        for (int i = 0; i < d; ++i) {
-            double a1 = 0.0, a2 = 0.0;
-            for (int k = 0; k < K; ++k)
-                for (int w = 0; w < waves; ++w) {
-                    a1 += hf[((size_t)k * 16 + w) * 2 * d + i];
-                    a2 += hf[((size_t)k * 16 + w) * 2 * d + d + i];
-                }
-            tmean[i] = a1 / ((double)K * Tp);
-            tsecond[i] = a2 / ((double)K * Tp);
-        }
+        std::copy_n(res.data() + 2 * Np + 1, d, tmean);
+        std::copy_n(res.data() + 2 * Np + 1 + d, d, tsecond);
     }
     *logZ = lz;
     if (!std::isfinite(lz)) return fail(OASMC_ENONFINITE, "log Z_PT is not finite");

@@ -1079,24 +1079,99 @@ hipError_t launch_target_eval(const EvalArgs& E, const ValuShape& s, hipStream_t
     return dispatch_all(6, E.a, s, 0, nullptr, 0, st, nullptr, &E);
 }
 
-// Column b of the tile sums over tiles in a fixed order (one wave per column).
-__global__ void __launch_bounds__(kWave) k_rejuv_reduce(const double* __restrict__ tsum,
-                                                         int64_t ntiles, int d, double samples,
-                                                         double* out)
+// Sum over the workgroup, in a fixed order (every thread gets it).
+template <int THREADS>
+__device__ __forceinline__ double block_sum(double v, double* shw)
 {
+    constexpr int W = THREADS / kWave;
+    v = wave_sum(v);
+    __syncthreads();  // shw may still be read from an earlier sum
+    if (threadIdx.x % kWave == 0) shw[threadIdx.x / kWave] = v;
+    __syncthreads();
+    double s = shw[0];
+#pragma unroll
+    for (int i = 1; i < W; ++i) s += shw[i];
+    return s;
+}
+
+// Column b of the tile sums over tiles in a fixed order.  Bound by the latency of
+// the column's loads (a cache line each, few columns): a workgroup of 16 waves per
+// column has them in flight at once (2^19 particles at d = 10: 85 -> 22 us).
+constexpr int kColThreads = 1024;
+__global__ void __launch_bounds__(kColThreads) k_rejuv_reduce(const double* __restrict__ tsum,
+                                                               int64_t ntiles, int d, double samples,
+                                                               double* out)
+{
+    __shared__ double shw[kColThreads / kWave];
     const int b = blockIdx.x;
     const int w = 2 * d + 1;
     double v = 0.0;
-    for (int64_t k = threadIdx.x; k < ntiles; k += kWave) v += tsum[(size_t)k * w + b];
-    v = wave_sum(v);
+    for (int64_t k = threadIdx.x; k < ntiles; k += kColThreads) v += tsum[(size_t)k * w + b];
+    v = block_sum<kColThreads>(v, shw);
     if (threadIdx.x == 0) out[b] = v / samples;
 }
 
 hipError_t launch_rejuv_reduce(const double* tsum, int64_t ntiles, int d, double samples,
                                double* out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_rejuv_reduce, dim3(2 * d + 1), dim3(kWave), 0, st, tsum, ntiles, d,
+    hipLaunchKernelGGL(k_rejuv_reduce, dim3(2 * d + 1), dim3(kColThreads), 0, st, tsum, ntiles, d,
                        samples, out);
+    return hipGetLastError();
+}
+
+// What the copies of parallel tempering leave, pooled over the copies: block n < N'
+// the stepping stone of temperature n over its K T' terms (res[n]) and the summed
+// rejections of pair n (res[N' + n]), block N' the round trips (res[2 N']), the
+// last 2 d blocks the target chain's averages (res[2 N' + 1 ..]).  Bound by latency;
+// the copies' records (8 MB for 2048 copies of 64 chains at d = 10) were pooled on
+// the host before (copy, page faults and exponentials: 1.4 ms of 3.67 for 512 steps,
+// now 15 us).
+constexpr int kPtRedThreads = 256;
+__global__ void __launch_bounds__(kPtRedThreads) k_pt_reduce(PtArgs A, int waves, double log_terms,
+                                                              double samples, double* res)
+{
+    __shared__ double shw[kPtRedThreads / kWave];
+    const int b = blockIdx.x, Np = A.Np, d = A.a.tg.d;
+    double v = 0.0;
+    if (b < Np) {
+        double M = -INFINITY;
+        for (int k = threadIdx.x; k < A.K; k += kPtRedThreads) {
+            const double* o = A.out + (size_t)k * A.stride;
+            if (o[2 * b + 1] > 0.0 && o[2 * b] > M) M = o[2 * b];
+            v += o[2 * Np + b];
+        }
+        v = block_sum<kPtRedThreads>(v, shw);
+        M = block_max<kPtRedThreads>(M, shw);
+        double s = 0.0;
+        for (int k = threadIdx.x; k < A.K; k += kPtRedThreads) {
+            const double mk = A.out[(size_t)k * A.stride + 2 * b];
+            const double sk = A.out[(size_t)k * A.stride + 2 * b + 1];
+            if (mk > -INFINITY && sk > 0.0) s += sk * exp(mk - M);
+        }
+        s = block_sum<kPtRedThreads>(s, shw);
+        if (threadIdx.x == 0) {
+            res[b] = (s > 0.0) ? M + log(s) - log_terms : -INFINITY;
+            res[Np + b] = v;
+        }
+        return;
+    }
+    if (b == Np) {
+        for (int k = threadIdx.x; k < A.K; k += kPtRedThreads) v += A.out[(size_t)k * A.stride + 3 * Np];
+    } else {
+        const int n = A.K * waves;
+        for (int e = threadIdx.x; e < n; e += kPtRedThreads)
+            v += A.fpart[((size_t)(e / waves) * 16 + e % waves) * 2 * d + (b - Np - 1)];
+    }
+    v = block_sum<kPtRedThreads>(v, shw);
+    if (threadIdx.x == 0) res[Np + b] = (b == Np) ? v : v / samples;
+}
+
+hipError_t launch_pt_reduce(const PtArgs& A, const ValuShape& s, double* res, hipStream_t st)
+{
+    const int P = kWave / s.lpp;
+    const int waves = (A.Np + P) / P;
+    hipLaunchKernelGGL(k_pt_reduce, dim3(A.Np + 1 + 2 * A.a.tg.d), dim3(kPtRedThreads), 0, st, A, waves,
+                       std::log((double)A.K * A.a.T), (double)A.K * A.a.T, res);
     return hipGetLastError();
 }
 

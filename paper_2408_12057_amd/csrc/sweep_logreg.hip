@@ -537,9 +537,10 @@ __device__ __forceinline__ void contraction(LogregShared& sh, const float* __res
     };
 #pragma unroll
     for (int kk = 0; kk < N32; ++kk) {
+        constexpr int F = N32 > 0 ? N32 : 1;
         const int k = N32 * w + kk;
         const floatx4 v = total(k);
-        const int g = k / (4 * N32), ft = k / 4 % N32, q0 = 4 * (k % 4);
+        const int g = k / (4 * F), ft = k / 4 % F, q0 = 4 * (k % 4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) sh.glp[32 * g + slot_row(q0 + i, h)][col_of(32 * ft + j, KH)] = v[i];
     }

@@ -1467,12 +1467,10 @@ __global__ void __launch_bounds__(kPtMaxThreads) k_pt(PtArgs A)
         if (tid < Np) {
             const double v = (A.beta[tid + 1] - A.beta[tid]) * Lsh[rep[tid]];
             if (v > -INFINITY) {
-                if (v > sm) {
-                    ss = ss * exp(sm - v) + 1.0;
-                    sm = v;
-                } else {
-                    ss += exp(v - sm);
-                }
+                const bool up = v > sm;
+                const double e = exp(up ? sm - v : v - sm);
+                ss = up ? ss * e + 1.0 : ss + e;
+                sm = up ? v : sm;
             }
         }
         if (live && tau[slot] == Np) {
