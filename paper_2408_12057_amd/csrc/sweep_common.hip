@@ -6,44 +6,85 @@
 
 namespace oasmc {
 
-// Merge the S slot partials of one entry (one wave per entry): each lane
-// takes slots lane, lane + 64, ... and the log-sum-exps are a maximum and then
-// a sum of exp(x - max), reduced in a fixed order (deterministic, and
-// independent of the grid): log_g[i*T + e] for e < T, the accept fraction,
-// and log Z_hat from entry T.
-__device__ __forceinline__ void merge_entry(const double* __restrict__ part, int64_t S, int T,
-                                            int e, double (&L)[3], double& cnt)
+// Merge the S slot partials of one entry (one workgroup per entry): the
+// log-sum-exps are a maximum and then a sum of exp(x - max) in a fixed order,
+// that of one wave whose lanes take slots lane, lane + 64, ... (deterministic, and
+// independent of the grid): log_g[i*T + e] for e < T, the accept fraction, and
+// log Z_hat from entry T.  Bound by latency (a cache line a slot, few entries) and
+// the exponentials: the waves take groups of 64 slots in turn, and waves 0 to 2 add
+// one of the three columns each from LDS, group after group, in the order of the
+// slots (20011 HMC particles in segments: 37 -> 12 us a merge).
+constexpr int kEntryWaves = 8;
+constexpr int kEntryThreads = kEntryWaves * kWave;
+
+struct EntryShared {
+    double red[kEntryWaves][4];
+    double term[2][kEntryWaves][3][kWave];
+    double L[3];
+};
+
+__device__ __forceinline__ void merge_entry(EntryShared& sh, const double* __restrict__ part, int64_t S,
+                                            int T, int e, double (&L)[3], double& cnt)
 {
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
+    const double* col = part + (size_t)e * 4;
+    const size_t row = (size_t)(T + 1) * 4;
     double m[3] = {-INFINITY, -INFINITY, -INFINITY};
     double c = 0.0;
-    for (int64_t s = lane; s < S; s += kWave) {
-        const double* p = part + ((size_t)s * (T + 1) + e) * 4;
+    for (int64_t s = tid; s < S; s += kEntryThreads) {
+        const double* p = col + (size_t)s * row;
 #pragma unroll
         for (int i = 0; i < 3; ++i) m[i] = fmax(m[i], p[i]);
-        c += p[3];
+        c += p[3];  // counts: whole numbers, the same in any order
     }
-    double sum[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < 3; ++i) m[i] = wave_max(m[i]);
-    for (int64_t s = lane; s < S; s += kWave) {
-        const double* p = part + ((size_t)s * (T + 1) + e) * 4;
+    c = wave_sum(c);
+    if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) sh.red[w][i] = m[i];
+        sh.red[w][3] = c;
+    }
+    __syncthreads();
+    cnt = 0.0;
+#pragma unroll
+    for (int u = 0; u < kEntryWaves; ++u) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) m[i] = fmax(m[i], sh.red[u][i]);
+        cnt += sh.red[u][3];
+    }
+    double sum = 0.0;
+    int buf = 0;
+    for (int64_t s0 = 0; s0 < S; s0 += kEntryThreads, buf ^= 1) {
+        const int64_t s = s0 + tid;
+        const double* p = col + (size_t)(s < S ? s : S - 1) * row;
 #pragma unroll
         for (int i = 0; i < 3; ++i)
-            if (m[i] > -INFINITY && p[i] > -INFINITY) sum[i] += exp(p[i] - m[i]);
-    }
+            sh.term[buf][w][i][lane] =
+                (s < S && m[i] > -INFINITY && p[i] > -INFINITY) ? exp(p[i] - m[i]) : 0.0;
+        __syncthreads();
+        if (w < 3) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) L[i] = lse_value(m[i], wave_sum(sum[i]));
-    cnt = wave_sum(c);
+            for (int u = 0; u < kEntryWaves; ++u) sum += sh.term[buf][u][w][lane];
+        }
+    }
+    if (w < 3) {
+        const double l = lse_value(w == 0 ? m[0] : (w == 1 ? m[1] : m[2]), wave_sum(sum));
+        if (lane == 0) sh.L[w] = l;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 3; ++i) L[i] = sh.L[i];
 }
 
-__global__ void __launch_bounds__(kWave) k_merge_slots(const double* __restrict__ part, int64_t S,
+__global__ void __launch_bounds__(kEntryThreads) k_merge_slots(const double* __restrict__ part, int64_t S,
                                                        int T, int64_t N, double* log_g, double* acc,
                                                        double* logZ)
 {
     const int e = blockIdx.x;
     double L[3], cnt;
-    merge_entry(part, S, T, e, L, cnt);
+    __shared__ EntryShared sh;
+    merge_entry(sh, part, S, T, e, L, cnt);
     if (threadIdx.x != 0) return;
     if (e < T) {
 #pragma unroll
@@ -68,22 +109,28 @@ __device__ __forceinline__ int merge_blocks(int64_t ntiles)
     return (int)(nb < kAsmcMergeBlocks ? nb : kAsmcMergeBlocks);
 }
 
-// Second level, by one wave: the block records, the moments, ESS and CESS,
-// the event decision and the log Z_hat increment.
+// Second level, by the four waves of a block: wave i forms log-sum-exp i of the block
+// records; then one thread the moments, ESS and CESS, the event decision and the
+// log Z_hat increment.
 __device__ __forceinline__ void asmc_merge_final(const SweepArgs& a, const AsmcState& z, int t,
-                                                 int trigger, double nu, int lane)
+                                                 int trigger, double nu, double (&shl)[4])
 {
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
     const int nb = merge_blocks(a.ntiles);
     const double* rec = z.blk_part + (size_t)lane * 8;
     const bool have = lane < nb;
-    double L[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) L[i] = wave_lse(have ? rec[i] : -INFINITY);
+    const double v = have ? rec[w] : -INFINITY;
     const double mx = wave_max(have ? rec[4] : -INFINITY);
     const double total = wave_sum(have ? rec[5] : 0.0);
-    if (lane != 0) return;
-    const int T = a.T;
     const double logN = log((double)a.N);
+    const double l = wave_lse(v);
+    if (lane == 0) shl[w] = l;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double L[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) L[i] = shl[i];
+    const int T = a.T;
     for (int i = 0; i < 3; ++i) z.log_g[(size_t)i * T + (t - 1)] = L[i];
     z.accept[t - 1] = total;
     const double rel_ess = exp(2.0 * L[1] - L[3] - logN);
@@ -138,14 +185,10 @@ __global__ void __launch_bounds__(kMergeThreads) k_asmc_merge(SweepArgs a, AsmcS
         shm[w][5] = cnt;
     }
     __syncthreads();
-    if (tid == 0) {
-#pragma unroll
-        for (int i = 0; i < 6; ++i) res[i] = shm[0][i];
-        for (int ww = 1; ww < W; ++ww) {
-#pragma unroll
-            for (int i = 0; i < 5; ++i) res[i] = fmax(res[i], shm[ww][i]);
-            res[5] += shm[ww][5];
-        }
+    if (tid < 6) {
+        double v = shm[0][tid];
+        for (int ww = 1; ww < W; ++ww) v = (tid < 5) ? fmax(v, shm[ww][tid]) : v + shm[ww][tid];
+        res[tid] = v;
     }
     __syncthreads();
     double M[4];
@@ -167,51 +210,56 @@ __global__ void __launch_bounds__(kMergeThreads) k_asmc_merge(SweepArgs a, AsmcS
         for (int i = 0; i < 4; ++i) shm[w][i] = sm[i];
     }
     __syncthreads();
-    if (tid == 0) {
+    if (tid < 6) {
+        // thread i records statistic i; the wave's fence stands between the
+        // records and the arrival
         double* out = z.blk_part + (size_t)blockIdx.x * 8;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            double acc = shm[0][i];
-            for (int ww = 1; ww < W; ++ww) acc += shm[ww][i];
-            out[i] = lse_value(M[i], acc);
+        if (tid < 4) {
+            double acc = shm[0][tid];
+            for (int ww = 1; ww < W; ++ww) acc += shm[ww][tid];
+            out[tid] = lse_value(res[tid], acc);
+        } else {
+            out[tid] = res[tid];
         }
-        out[4] = res[4];
-        out[5] = res[5];
+        __threadfence();
     }
     // the last block to finish merges the block records; the arrival counter
     // only elects that block (no block waits for another)
     __shared__ bool last;
-    if (tid == 0) {
-        __threadfence();  // this block's record before its arrival
-        last = atomicAdd(z.ticket, 1u) == (unsigned)(nb - 1);
-    }
+    if (tid == 0) last = atomicAdd(z.ticket, 1u) == (unsigned)(nb - 1);
     __syncthreads();
     if (!last) return;
     __threadfence();  // the other blocks' records
-    if (w == 0) asmc_merge_final(a, z, t, trigger, nu, lane);
+    __shared__ double shl[4];
+    asmc_merge_final(a, z, t, trigger, nu, shl);
     if (tid == 0) z.ticket[0] = 0u;
 }
 
-// Merge of one segment between resampling times fixed in advance (one wave
+// Merge of one segment between resampling times fixed in advance (one workgroup
 // per entry, the slot order of k_merge_slots): blocks 0 .. t_end - t_begin - 1
 // take the entries of steps t_begin + 1 .. t_end (moments, accepted counts; no
 // per-step ESS), the last block entry T, whose log-sum-exp of the segment's
 // final log-weights gives the log Z_hat factor of this event and whose fourth
 // field holds the largest log w (the shift of the resampler's integer
 // weights).  Each output element is written by one block.
-__global__ void __launch_bounds__(kWave) k_seg_merge(SweepArgs a, AsmcState z)
+__global__ void __launch_bounds__(kEntryThreads) k_seg_merge(SweepArgs a, AsmcState z)
 {
     const int T = a.T;
     const int nsteps = a.t_end - a.t_begin;
     const bool fin = (int)blockIdx.x == nsteps;
     const int e = fin ? T : a.t_begin + (int)blockIdx.x;
     double L[3], cnt;
-    merge_entry(a.part, a.S, T, e, L, cnt);
+    __shared__ EntryShared sh;
+    merge_entry(sh, a.part, a.S, T, e, L, cnt);
     double mx = -INFINITY;
     if (fin) {
-        for (int64_t s = threadIdx.x; s < a.S; s += kWave)
+        for (int64_t s = threadIdx.x; s < a.S; s += kEntryThreads)
             mx = fmax(mx, a.part[((size_t)s * (T + 1) + T) * 4 + 3]);
         mx = wave_max(mx);
+        if (threadIdx.x % kWave == 0) sh.red[threadIdx.x / kWave][0] = mx;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kEntryWaves; ++u) mx = fmax(mx, sh.red[u][0]);
     }
     if (threadIdx.x != 0) return;
     if (!fin) {
@@ -1307,14 +1355,14 @@ hipError_t launch_resample_step(const SweepArgs& a, const AsmcState& z, int t, b
 hipError_t launch_segment_merge(const SweepArgs& a, const AsmcState& z, hipStream_t st)
 {
     const int nsteps = a.t_end - a.t_begin;
-    hipLaunchKernelGGL(k_seg_merge, dim3(nsteps + 1), dim3(kWave), 0, st, a, z);
+    hipLaunchKernelGGL(k_seg_merge, dim3(nsteps + 1), dim3(kEntryThreads), 0, st, a, z);
     return hipGetLastError();
 }
 
 hipError_t launch_merge_slots(const double* part, int64_t S, int T, int64_t N, double* log_g,
                               double* acc, double* logZ, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_merge_slots, dim3(T + 1), dim3(kWave), 0, st, part, S, T, N, log_g, acc,
+    hipLaunchKernelGGL(k_merge_slots, dim3(T + 1), dim3(kEntryThreads), 0, st, part, S, T, N, log_g, acc,
                        logZ);
     return hipGetLastError();
 }
