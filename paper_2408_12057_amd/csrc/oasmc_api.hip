@@ -115,13 +115,32 @@ struct oasmc_handle_s {
         *out = b.p;
         return hipSuccess;
     }
+
+    // Pinned host memory for the schedule and the outputs of one pass (grow-only).
+    Buf host;
+    hipError_t get_host(size_t bytes, void** out)
+    {
+        if (host.bytes < bytes) {
+            if (host.p) {
+                hipError_t e = hipHostFree(host.p);
+                if (e != hipSuccess) return e;
+                host.p = nullptr;
+                host.bytes = 0;
+            }
+            hipError_t e = hipHostMalloc(&host.p, bytes, hipHostMallocDefault);
+            if (e != hipSuccess) return e;
+            host.bytes = bytes;
+        }
+        *out = host.p;
+        return hipSuccess;
+    }
 };
 
 namespace {
 
 enum BufId {
     B_BETA, B_EPS, B_PART, B_LOGG, B_ACC, B_SCAL, B_X, B_X2, B_ELL, B_ELL2, B_LW, B_ACCW,
-    B_TPART, B_NRES, B_ESS, B_RES, B_C, B_BTOT, B_LWO, B_XO, B_LOGREG, B_CKPT, B_SEG, B_ABITS,
+    B_TPART, B_C, B_BTOT, B_LWO, B_XO, B_LOGREG, B_CKPT, B_SEG, B_ABITS,
     B_GPART, B_GRAD, B_DEVRUN, B_DEVDESC, B_G, B_G2, B_BLK, B_RJ_ANC, B_RJ_SUM, B_RJ_OUT,
     B_RJ_LW, B_RJ_X, B_ZSTOP, B_PT_OUT, B_PT_F, B_PT_RES, B_COUNT
 };
@@ -931,6 +950,7 @@ int oasmc_handle_destroy(oasmc_handle* h)
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     for (auto& b : h->bufs)
         if (b.p) (void)hipFree(b.p);
+    if (h->host.p) (void)hipHostFree(h->host.p);
     delete h;
     return OASMC_OK;
 }
@@ -1023,18 +1043,32 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
     a.acc_bits = out->accept_bits;
     a.acc_words = (T + 31) / 32;
 
-    double *dbeta, *deps, *dlogg, *dacc, *dscal;
-    HIP_TRY(wget(h, B_BETA, T + 1, &dbeta));
-    HIP_TRY(wget(h, B_EPS, T, &deps));
-    HIP_TRY(wget(h, B_LOGG, 3 * (size_t)T, &dlogg));
-    HIP_TRY(wget(h, B_ACC, T, &dacc));
-    HIP_TRY(wget(h, B_SCAL, 8, &dscal));
-    HIP_TRY(hipMemcpyAsync(dbeta, beta, sizeof(double) * (T + 1), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(deps, eps, sizeof(double) * T, hipMemcpyHostToDevice, st));
+    // the schedule goes in one copy and the outputs come back in one, through
+    // pinned memory (each pageable copy stops the host for some 10 us):
+    // beta [T + 1], eps [T]; and log_g [3 T], accept [T], scal [8], ess [T],
+    // nres [4] and resampled [T] (whole numbers)
+    const size_t nin = 2 * (size_t)T + 1;
+    const size_t nout = 5 * (size_t)T + 8 + (4 + (size_t)T + 1) / 2;
+    double *dbeta, *dlogg, *hin;
+    HIP_TRY(wget(h, B_BETA, nin, &dbeta));
+    HIP_TRY(wget(h, B_LOGG, nout, &dlogg));
+    HIP_TRY(h->get_host(sizeof(double) * (nin + nout), (void**)&hin));
+    double* const deps = dbeta + T + 1;
+    double* const dacc = dlogg + 3 * (size_t)T;
+    double* const dscal = dacc + T;
+    double* const dess = dscal + 8;
+    int* const dnres = reinterpret_cast<int*>(dess + T);
+    const double* const hout = hin + nin;
+    const double* const scal = hout + 4 * (size_t)T;
+    std::copy_n(beta, T + 1, hin);
+    std::copy_n(eps, T, hin + T + 1);
+    // (after a shape has been measured: its trial passes use the same buffer)
+    auto send_schedule = [&] {
+        return hipMemcpyAsync(dbeta, hin, sizeof(double) * nin, hipMemcpyHostToDevice, st);
+    };
     a.beta = dbeta;
     a.eps = deps;
 
-    std::vector<double> scal(8, 0.0);
     int nres = 0;
     if (!kernel->resample) {
         int64_t ntiles;
@@ -1052,6 +1086,7 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
             if (ps) return ps;
             ntiles = valu_tiles(N, shape);
         }
+        HIP_TRY(send_schedule());
         const int64_t S = slot_count(ntiles, kernel->slots);
         double* part;
         HIP_TRY(wget(h, B_PART, (size_t)S * (T + 1) * 4, &part));
@@ -1072,10 +1107,10 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
         }
         if (h->prof) HIP_TRY(hipEventRecord(h->ev1, st));
         HIP_TRY(launch_merge_slots(part, S, T, N, dlogg, dacc, dscal, st));
-        HIP_TRY(hipMemcpyAsync(out->log_g, dlogg, sizeof(double) * 3 * T, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(out->accept, dacc, sizeof(double) * T, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(scal.data(), dscal, sizeof(double), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(hin + nin, dlogg, sizeof(double) * (4 * (size_t)T + 1), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
+        std::copy_n(hout, 3 * (size_t)T, out->log_g);
+        std::copy_n(hout + 3 * (size_t)T, T, out->accept);
         if (h->prof) {
             float ms = 0.f;
             HIP_TRY(hipEventElapsedTime(&ms, h->ev0, h->ev1));
@@ -1094,6 +1129,7 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
         ValuShape shape{};
         if (!valu_shape(problem->d, N, &shape))
             return fail(OASMC_EUNSUPPORTED, "no kernel shape for d=%d", problem->d);
+        HIP_TRY(send_schedule());
         const int64_t ntiles = valu_tiles(N, shape);
         const int d = problem->d;
         AsmcState z{};
@@ -1109,9 +1145,9 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
         HIP_TRY(wget(h, B_ACCW, N, &z.accw));
         HIP_TRY(wget(h, B_TPART, (size_t)ntiles * 8, &z.tile_part));
         HIP_TRY(wget(h, B_BLK, (size_t)kAsmcMergeBlocks * 8, &z.blk_part));
-        HIP_TRY(wget(h, B_NRES, 4, &z.nres));
-        HIP_TRY(wget(h, B_ESS, T, &z.ess));
-        HIP_TRY(wget(h, B_RES, T, &z.resampled));
+        z.nres = dnres;
+        z.ess = dess;
+        z.resampled = dnres + 4;
         HIP_TRY(wget(h, B_C, N, &z.C));
         HIP_TRY(wget(h, B_BTOT, resample_words(N), &z.btot));
         z.ticket = reinterpret_cast<unsigned*>(z.nres + 1);  // cleared with nres below
@@ -1161,21 +1197,17 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
             }
             if (h->prof) HIP_TRY(hipEventRecord(h->ev1, st));
         }
-        std::vector<double> cnt(T);
-        HIP_TRY(hipMemcpyAsync(out->log_g, dlogg, sizeof(double) * 3 * T, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(cnt.data(), dacc, sizeof(double) * T, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(scal.data(), dscal, sizeof(double) * 8, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(&nres, z.nres, sizeof(int), hipMemcpyDeviceToHost, st));
-        if (out->ess)
-            HIP_TRY(hipMemcpyAsync(out->ess, z.ess, sizeof(double) * T, hipMemcpyDeviceToHost, st));
-        if (out->resampled)
-            HIP_TRY(hipMemcpyAsync(out->resampled, z.resampled, sizeof(int) * T,
-                                   hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(hin + nin, dlogg, sizeof(double) * nout, hipMemcpyDeviceToHost, st));
         if (out->lw) HIP_TRY(hipMemcpyAsync(out->lw, z.lw, sizeof(double) * N, hipMemcpyDeviceToDevice, st));
         if (out->x)
             HIP_TRY(hipMemcpyAsync(out->x, z.X, sizeof(float) * N * d, hipMemcpyDeviceToDevice, st));
         HIP_TRY(hipStreamSynchronize(st));
-        for (int t = 0; t < T; ++t) out->accept[t] = cnt[t] / (double)N;
+        const int* const hres = reinterpret_cast<const int*>(scal + 8 + T);
+        nres = hres[0];
+        std::copy_n(hout, 3 * (size_t)T, out->log_g);
+        for (int t = 0; t < T; ++t) out->accept[t] = hout[3 * (size_t)T + t] / (double)N;
+        if (out->ess) std::copy_n(scal + 8, T, out->ess);
+        if (out->resampled) std::copy_n(hres + 4, T, out->resampled);
         if (h->prof) {
             // one "launch" per step: the step's sweep, merge and resampler
             float ms = 0.f;
