@@ -26,8 +26,7 @@ FLAGS = [
 # registers a lane for the whole kernel, and what spills for them costs more than
 # the moves saved (a logistic-regression run 664 -> 648 ms, the d = 100 mixture
 # HMC step 155 -> 126 us, a d = 100 Gaussian MALA run 6.0 -> 4.4 ms).  The
-# selection of the next inverse temperature in sweep_common has registers to
-# spare and is 12 % faster with them hoisted.
+# other sources hold no such loop.
 IN_PLACE_CONSTANTS = ["-mllvm", "-disable-machine-licm"]
 IN_PLACE_SOURCES = ("valu_", "sweep_logreg", "adjoint")
 
