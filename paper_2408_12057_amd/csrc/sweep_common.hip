@@ -98,9 +98,9 @@ __global__ void __launch_bounds__(kEntryThreads) k_merge_slots(const double* __r
 // The per-step merge of the resampling variant, in two levels with a fixed
 // order (deterministic, independent of timing): block b of the first level
 // reduces a contiguous range of tile records to one record (log-sum-exps as a
-// maximum and then a sum of exp(x - max)); one wave of the last block to
-// finish then merges the block records, records the moments, ESS and CESS,
-// decides the event and adds the log Z_hat increment (one launch).
+// maximum and then a sum of exp(x - max)); the last block to finish then
+// merges the block records, records the moments, ESS and CESS, decides the
+// event and adds the log Z_hat increment (one launch).
 constexpr int kMergeThreads = 256;
 
 __device__ __forceinline__ int merge_blocks(int64_t ntiles)
@@ -211,8 +211,8 @@ __global__ void __launch_bounds__(kMergeThreads) k_asmc_merge(SweepArgs a, AsmcS
     }
     __syncthreads();
     if (tid < 6) {
-        // thread i records statistic i; the wave's fence stands between the
-        // records and the arrival
+        // thread i records statistic i; its fence and the barrier stand between
+        // every record and the arrival
         double* out = z.blk_part + (size_t)blockIdx.x * 8;
         if (tid < 4) {
             double acc = shm[0][tid];
@@ -223,6 +223,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_asmc_merge(SweepArgs a, AsmcS
         }
         __threadfence();
     }
+    __syncthreads();
     // the last block to finish merges the block records; the arrival counter
     // only elects that block (no block waits for another)
     __shared__ bool last;
