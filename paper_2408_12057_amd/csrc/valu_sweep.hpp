@@ -350,9 +350,9 @@ struct Particle {
     // that leave each lane its own components (13 instructions for four, against 32
     // for sums that every lane holds, and the comparison is made once).  States and means are binary32, so a difference is
     // off by 2^-24 of itself and a distance, its scaling and the comparison by
-    // less than 64 such roundings (4e-6); exp underflows to zero below -746.  False
-    // when some particle of the wave has more than half the components near (or a
-    // distance is not finite: then every comparison keeps its component).
+    // less than 64 such roundings (4e-6); exp underflows to zero below -746.  A
+    // component whose distance or exponent is not finite in binary32 is kept.  False
+    // when some particle of the wave has more than half the components near.
     static __device__ __forceinline__ bool near_components(const TargetDev& tg, const ParView& pv,
                                                            int r, const float (&x)[DPL],
                                                            uint32_t& near)
@@ -406,9 +406,11 @@ struct Particle {
                 }
                 const float e = sq[v] * (float)pv.hiv[k];
                 lo = (k < K) ? fmaxf(lo, -e * (1.f + slack)) : lo;
+                // (beyond binary32 its true exponent may lie anywhere below lo)
+                const float above = e < INFINITY ? -e * (1.f - slack) : INFINITY;
 #pragma unroll
                 for (int q = 0; q < KO; ++q)
-                    if (k == q * LPP + r) hi[q] = -e * (1.f - slack);
+                    if (k == q * LPP + r) hi[q] = above;
             }
         }
         lo = fmaxf(lo, dpp_f32<kDppXor1>(lo));
