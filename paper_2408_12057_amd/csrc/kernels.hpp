@@ -159,7 +159,7 @@ struct AsmcState {
     double* G2;        // [N*d] gather target of G
     double* lw;        // [N]
     uint32_t* accw;    // [N] accept bits of the current 32-step word
-    double* tile_part; // [ntiles*8]
+    double* tile_part; // [ntiles*8]: six statistics, and [6] look_in_vain of the tile
     double* blk_part;  // [kAsmcMergeBlocks*8] per-block merge of tile_part
     // scalars updated on the device
     double* scal;      // [0] log Z_hat, [1] max(lw) at event, [2] flag, [3] u word

@@ -122,8 +122,27 @@ __device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char*
 // exact zeros in x, z, the momentum and the gradient, and the lane-layout
 // means are zero there too, so every coordinate loop runs without a branch:
 // a padded coordinate adds +0 to each sum and stays +0 through every move.
+// Trajectories of a tile that go without looking for near components: none while
+// looking finds few, then 1, 3, 7 and at most 15 after each look in vain (the
+// number left in the low four bits, the last length above them).  A look costs
+// about a third of an evaluation.  Mixtures of 8 components at d = 100, 24 steps of 5
+// leapfrog steps, N = 20011: overlapping 1.49 ms without looking, 1.56 with a look a
+// trajectory, 1.51 so; far apart 1.58, 0.87 and 0.87.
+__device__ __forceinline__ int look_in_vain(int wait)
+{
+    const int n = min(2 * (wait >> 4) + 1, 15);
+    return (n << 4) | n;
+}
+
 template <int FAM, int LPP, int DPL>
 struct Particle {
+    // A mixture over lanes of 16 coordinates has no registers left in a trajectory:
+    // coordinates are then converted where they are used, components taken one by one
+    // and ell formed at every evaluation (24 HMC steps of 70000 overlapping particles at
+    // d = 30: 1.97 ms otherwise, 1.53 so; with 8 coordinates a lane, d = 100 and
+    // N = 20011, 1.56 so and 1.51 otherwise).
+    static constexpr bool kRoomy = FAM != kGmm || LPP == 1 || DPL <= 8;
+
     // reference mean and target mean k at this lane's coordinate j
     static __device__ __forceinline__ double ref(const ParView& pv, int r, int j)
     {
@@ -154,18 +173,41 @@ struct Particle {
         return x[0] > 0.f && (double)x[0] < tg.box && x[1] > 0.f && (double)x[1] < tg.box;
     }
 
+    // The coordinates in binary64, behind an empty asm: converted once and kept, where
+    // the compiler would convert them again at each component (a third of a
+    // component's instructions in the trajectories of a mixture over lanes).
+    static __device__ __forceinline__ void widen(const float (&x)[DPL], double (&xd)[DPL])
+    {
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) {
+            xd[j] = (double)x[j];
+            if constexpr (kRoomy) asm("" : "+v"(xd[j]));
+        }
+    }
+
+    // |x - m_ref|^2 over the particle's lanes.
+    template <typename X>
+    static __device__ __forceinline__ double ref_square(const ParView& pv, int r,
+                                                        const X (&x)[DPL])
+    {
+        double sse = 0.0;
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) {
+            const double b = (double)x[j] - ref(pv, r, j);
+            sse = fma(b, b, sse);
+        }
+        return group_sum<LPP>(sse);
+    }
+
     // ell(x) = log gamma(x) - log eta(x); with GRAD also its gradient on this
     // lane's coordinates.  r = lane index inside the group.
-    // few (mixtures over several lanes): in, whether to look for the components
-    // that matter; out, whether they were at most half of them.
-    // value: whether ell itself is wanted (else 0 comes back: within a trajectory
+    // VALUE: whether ell itself is wanted (else 0 may come back): within a trajectory
     // only the gradient is, and the sums over the lanes and the logarithm are not
-    // formed).
-    template <bool GRAD>
+    // formed.
+    template <bool GRAD, bool VALUE = true>
     static __device__ __forceinline__ double eval(const TargetDev& tg, const Consts& c,
                                                   const ParView& pv0, int r, const float (&x)[DPL],
-                                                  double (&g)[DPL], bool* few = nullptr,
-                                                  bool value = true)
+                                                  double (&g)[DPL])
     {
         const ParView pv = fresh(pv0);
         if constexpr (FAM == kUnid) {
@@ -184,7 +226,7 @@ struct Particle {
             return k * log1p((u - p) / p) + (n - k) * log1p(-(u - p) / (1.0 - p));
         } else if constexpr (FAM == kGauss) {
             double ssg = 0.0, sse = 0.0;
-            if (GRAD && !value) {
+            if constexpr (GRAD && !VALUE) {
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
                     const double xv = (double)x[j];
@@ -208,24 +250,15 @@ struct Particle {
         } else {
             // equal-weight mixture of unnormalised isotropic components, streamed
             // over k with a running maximum (log-sum-exp and responsibilities)
-            double sse = 0.0;
+            if constexpr (LPP > 1) {
+                double xd[DPL];
+                widen(x, xd);
+                return mixture_multilane<GRAD, VALUE>(tg, c, pv, r, xd, g);
+            }
+            const double sse = VALUE ? ref_square(pv, r, x) : 0.0;
 #pragma unroll
             for (int j = 0; j < DPL; ++j)
                 if (GRAD) g[j] = 0.0;
-            if (value) {
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    const double b = (double)x[j] - ref(pv, r, j);
-                    sse = fma(b, b, sse);
-                }
-                sse = group_sum<LPP>(sse);
-            }
-            if constexpr (LPP > 1) {
-                uint32_t near;
-                if (few && *few && (*few = near_components(tg, pv, r, x, near)))
-                    return mixture_few<GRAD>(tg, c, pv, r, x, g, sse, near, value);
-                return mixture_multilane<GRAD>(tg, c, pv, r, x, g, sse, value);
-            }
             double mx = -INFINITY, s = 0.0;
 #pragma unroll 1
             for (int k = 0; k < tg.K; ++k) {
@@ -257,7 +290,7 @@ struct Particle {
                         g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
                 }
             }
-            const double lse = value ? mx + log(s) - c.logK : 0.0;
+            const double lse = VALUE ? mx + log(s) - c.logK : 0.0;
             if (GRAD) {
                 const double inv_s = 1.0 / s;
 #pragma unroll
@@ -275,13 +308,16 @@ struct Particle {
     // log sum_k exp(e_k - M); the gradient gathers the weights from their
     // lanes.  (Streaming over k on every lane would repeat each exponential
     // LPP times.)
-    template <bool GRAD>
+    template <bool GRAD, bool VALUE>
     static __device__ __forceinline__ double mixture_multilane(const TargetDev& tg, const Consts& c,
                                                                const ParView& pv, int r,
-                                                               const float (&x)[DPL],
-                                                               double (&g)[DPL], double sse,
-                                                               bool value)
+                                                               const double (&x)[DPL],
+                                                               double (&g)[DPL])
     {
+        const double sse = VALUE ? ref_square(pv, r, x) : 0.0;
+#pragma unroll
+        for (int j = 0; j < DPL; ++j)
+            if (GRAD) g[j] = 0.0;
         constexpr int KO = (kMaxK + LPP - 1) / LPP;  // components owned by a lane
         const int K = tg.K;
         double eo[KO];
@@ -292,27 +328,27 @@ struct Particle {
         // interleave; the lane layout and 1/(2 v_k) are zero-padded to whole
         // blocks and a padded component gets e_k = -inf (weight 0)
         double M = -INFINITY;
-#pragma unroll 1
-        for (int k0 = 0; k0 < K; k0 += kKBlock) {
-            double sq[kKBlock];
 #pragma unroll
-            for (int u = 0; u < kKBlock; ++u) {
-                sq[u] = 0.0;
+        for (int k0 = 0; k0 < kMaxK; k0 += kKBlock) {
+            if (k0 < K) {
+                double sq[kKBlock];
 #pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    const double a = (double)x[j] - mean(pv, k0 + u, r, j);
-                    sq[u] = fma(a, a, sq[u]);
+                for (int u = 0; u < kKBlock; ++u) {
+                    sq[u] = 0.0;
+#pragma unroll
+                    for (int j = 0; j < DPL; ++j) {
+                        const double a = x[j] - mean(pv, k0 + u, r, j);
+                        sq[u] = fma(a, a, sq[u]);
+                    }
                 }
-            }
 #pragma unroll
-            for (int u = 0; u < kKBlock; ++u) {
-                const int k = k0 + u;
-                double ek = -group_sum<LPP>(sq[u]) * pv.hiv[k];
-                if (k >= K) ek = -INFINITY;
-                M = fmax(M, ek);
-#pragma unroll
-                for (int q = 0; q < KO; ++q)
-                    if (k == q * LPP + r) eo[q] = ek;
+                for (int u = 0; u < kKBlock; ++u) {
+                    const int k = k0 + u;
+                    double ek = -group_sum<LPP>(sq[u]) * pv.hiv[k];
+                    if (k >= K) ek = -INFINITY;
+                    M = fmax(M, ek);
+                    if ((k % LPP) == r) eo[k / LPP] = ek;
+                }
             }
         }
         double wo[KO];
@@ -323,23 +359,32 @@ struct Particle {
             so += wo[q];
         }
         const double s = group_sum<LPP>(so);
-        const double lse = value ? M + log(s) - c.logK : 0.0;
+        const double lse = VALUE ? M + log(s) - c.logK : 0.0;
         if (GRAD) {
             const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
-#pragma unroll 1
-            for (int k = 0; k < K; ++k) {
-                double w = wo[0];
-#pragma unroll
-                for (int q = 1; q < KO; ++q) w = (k / LPP == q) ? wo[q] : w;
-                const double f = __shfl(w, base + k % LPP, kWave) * pv.iv[k];
+            auto pull = [&](int k) {
+                const double f = __shfl(wo[k / LPP], base + k % LPP, kWave) * pv.iv[k];
 #pragma unroll
                 for (int j = 0; j < DPL; ++j)
-                    g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
+                    g[j] = fma(f, mean(pv, k, r, j) - x[j], g[j]);
+            };
+            // where there are registers for it whole blocks without a branch inside,
+            // as above, and the rest one by one
+#pragma unroll
+            for (int k0 = 0; k0 < kMaxK; k0 += kKBlock) {
+                if (kRoomy && k0 + kKBlock <= K) {
+#pragma unroll
+                    for (int u = 0; u < kKBlock; ++u) pull(k0 + u);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < (kRoomy ? kKBlock - 1 : kKBlock); ++u)
+                        if (k0 + u < K) pull(k0 + u);
+                }
             }
             const double inv_s = 1.0 / s;
 #pragma unroll
             for (int j = 0; j < DPL; ++j)
-                g[j] = g[j] * inv_s + ((double)x[j] - ref(pv, r, j)) * c.inv_s2r;
+                g[j] = g[j] * inv_s + (x[j] - ref(pv, r, j)) * c.inv_s2r;
         }
         return lse + sse * c.half_inv_s2r + c.cst_eta;
     }
@@ -352,7 +397,10 @@ struct Particle {
     // off by 2^-24 of itself and a distance, its scaling and the comparison by
     // less than 64 such roundings (4e-6); exp underflows to zero below -746.  A
     // component whose distance or exponent is not finite in binary32 is kept.  False
-    // when some particle of the wave has more than half the components near.
+    // when some particle of the wave has more than half the components near, or three
+    // eighths on two lanes a particle, where 32 particles share the walk (4 of 8 near,
+    // 24 steps: d = 30, N = 70000 1.95 ms by the walk and 1.53 all at once, d = 100,
+    // N = 20011 1.43 and 1.49).
     static __device__ __forceinline__ bool near_components(const TargetDev& tg, const ParView& pv,
                                                            int r, const float (&x)[DPL],
                                                            uint32_t& near)
@@ -422,7 +470,7 @@ struct Particle {
             const uint64_t bal = __ballot(q * LPP + r < K && !(hi[q] < lo - 746.f - slack * fabsf(lo)));
             near |= (uint32_t)((bal >> base) & ((1u << LPP) - 1u)) << (q * LPP);
         }
-        return __ballot(2 * __popc(near) > K) == 0;
+        return __ballot(__popc(near) > (LPP > 2 ? K / 2 : (3 * K + 7) / 8)) == 0;
     }
 
     // The mixture term from the components in `near` (bits, at least one): each
@@ -434,12 +482,16 @@ struct Particle {
     // instead of 496 (96 HMC steps of 20011 particles: 6.20 -> 3.93 ms, of which
     // 4.44 -> 3.93 come from ell formed at a trajectory's end only, one force an
     // evaluation and the reduction of near_components).
-    template <bool GRAD>
     static __device__ __forceinline__ double mixture_few(const TargetDev& tg, const Consts& c,
                                                          const ParView& pv, int r,
-                                                         const float (&x)[DPL], double (&g)[DPL],
-                                                         double sse, uint32_t near, bool value)
+                                                         const float (&xf)[DPL], double (&g)[DPL],
+                                                         uint32_t near, bool value)
     {
+        double x[DPL];
+        widen(xf, x);
+        const double sse = value ? ref_square(pv, r, x) : 0.0;
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) g[j] = 0.0;
         constexpr int KO = (kMaxK + LPP - 1) / LPP;
         if (__ballot((near & (near - 1u)) != 0u) == 0) {
             // one component a particle: its weight, their sum and its inverse are
@@ -453,20 +505,18 @@ struct Particle {
                 double sq = 0.0;
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
-                    const double a = (double)x[j] - mean(pv, k, r, j);
+                    const double a = x[j] - mean(pv, k, r, j);
                     sq = fma(a, a, sq);
                 }
                 double ek = -group_sum<LPP>(sq) * pv.hiv[k];
                 asm volatile("" : "+v"(ek));
                 lse = ek - c.logK;
             }
-            if (GRAD) {
-                const double f = pv.iv[k];
+            const double f = pv.iv[k];
 #pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
-                    g[j] = g[j] * inv_s + ((double)x[j] - ref(pv, r, j)) * c.inv_s2r;
-                }
+            for (int j = 0; j < DPL; ++j) {
+                g[j] = fma(f, mean(pv, k, r, j) - x[j], g[j]);
+                g[j] = g[j] * inv_s + (x[j] - ref(pv, r, j)) * c.inv_s2r;
             }
             return lse + sse * c.half_inv_s2r + c.cst_eta;
         }
@@ -480,7 +530,7 @@ struct Particle {
             double sq = 0.0;
 #pragma unroll
             for (int j = 0; j < DPL; ++j) {
-                const double a = (double)x[j] - mean(pv, k, r, j);
+                const double a = x[j] - mean(pv, k, r, j);
                 sq = fma(a, a, sq);
             }
             const double ek = -group_sum<LPP>(sq) * pv.hiv[k];
@@ -502,25 +552,23 @@ struct Particle {
         }
         const double s = group_sum<LPP>(so);
         const double lse = value ? M + log(s) - c.logK : 0.0;
-        if (GRAD) {
-            for (; __ballot(left != 0u) != 0; left &= left - 1u) {
-                const bool on = left != 0u;
-                const int k = on ? __ffs(left) - 1 : 0;
-                double w = wo[0];
+        for (; __ballot(left != 0u) != 0; left &= left - 1u) {
+            const bool on = left != 0u;
+            const int k = on ? __ffs(left) - 1 : 0;
+            double w = wo[0];
 #pragma unroll
-                for (int q = 1; q < KO; ++q) w = (k / LPP == q) ? wo[q] : w;
-                // (the owner's lane holds component k in the same register as here)
-                const double f = __shfl(w, base + k % LPP, kWave) * pv.iv[k];
-                if (on) {
+            for (int q = 1; q < KO; ++q) w = (k / LPP == q) ? wo[q] : w;
+            // (the owner's lane holds component k in the same register as here)
+            const double f = __shfl(w, base + k % LPP, kWave) * pv.iv[k];
+            if (on) {
 #pragma unroll
-                    for (int j = 0; j < DPL; ++j) g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
-                }
+                for (int j = 0; j < DPL; ++j) g[j] = fma(f, mean(pv, k, r, j) - x[j], g[j]);
             }
-            const double inv_s = 1.0 / s;
-#pragma unroll
-            for (int j = 0; j < DPL; ++j)
-                g[j] = g[j] * inv_s + ((double)x[j] - ref(pv, r, j)) * c.inv_s2r;
         }
+        const double inv_s = 1.0 / s;
+#pragma unroll
+        for (int j = 0; j < DPL; ++j)
+            g[j] = g[j] * inv_s + (x[j] - ref(pv, r, j)) * c.inv_s2r;
         return lse + sse * c.half_inv_s2r + c.cst_eta;
     }
 
@@ -604,7 +652,7 @@ struct Particle {
                                                 const ParView& pv, const RngKey& key, uint32_t n,
                                                 uint32_t t, int r, int L, double beta, double eps,
                                                 float (&x)[DPL], double& ell, double (&g)[DPL],
-                                                int forced = -1)
+                                                int forced = -1, int* wait = nullptr)
     {
         // RWMH draws its normals block by block inside the proposal loop
         // (shorter live ranges); MALA and HMC draw them all first
@@ -658,7 +706,7 @@ struct Particle {
         double gp[DPL];
         double ellp;
         const bool acc = propose<MOVE>(tg, c, pv, key, n, t, r, L, beta, eps, x, ell, g, xp, ellp, gp,
-                                       forced);
+                                       forced, wait);
         if (acc) {
 #pragma unroll
             for (int j = 0; j < DPL; ++j) {
@@ -679,7 +727,8 @@ struct Particle {
                                                    uint32_t t, int r, int L, double beta, double eps,
                                                    const float (&x)[DPL], double ell,
                                                    const double (&g)[DPL], float (&xp)[DPL],
-                                                   double& ellp, double (&gp)[DPL], int forced = -1)
+                                                   double& ellp, double (&gp)[DPL], int forced = -1,
+                                                   int* wait = nullptr)
     {
         double z[DPL];
         if constexpr (uses_grad(MOVE)) normals(pv, key, n, t, kStreamMove, r, tg.d, z);
@@ -745,21 +794,51 @@ struct Particle {
 #pragma unroll
             for (int j = 0; j < DPL; ++j)
                 force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
-            // the first evaluation of a trajectory looks for the components near
-            // its particles; the others do where that found few
-            bool few = pv.lmf != nullptr;
-            for (int l = 0; l < L; ++l) {
+            auto drift = [&] {
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
                     mom[j] += he * force[j];
                     xp[j] = (float)((double)xp[j] + eps * mom[j]);
                 }
-                ellp = eval<true>(tg, c, pv, r, xp, gp, &few, l + 1 == L);
+            };
+            auto kick = [&] {
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
                     force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
                     mom[j] += he * force[j];
                 }
+            };
+            int l = 0;
+            bool drifted = false;  // the position of step l is there already
+            if constexpr (FAM == kGmm && LPP > 1) {
+                if (pv.lmf && tg.K > 1 && (!wait || (*wait & 15) == 0)) {
+                    for (; l < L && !drifted; l += drifted ? 0 : 1) {
+                        drift();
+                        const ParView pf = fresh(pv);
+                        uint32_t near;
+                        if (near_components(tg, pf, r, xp, near)) {
+                            ellp = mixture_few(tg, c, pf, r, xp, gp, near, l + 1 == L);
+                            kick();
+                        } else {
+                            drifted = true;
+                        }
+                    }
+                    if (wait) *wait = (drifted && l == 0) ? look_in_vain(*wait) : 0;
+                } else if (wait && (*wait & 15)) {
+                    --*wait;
+                }
+            }
+            // ell is wanted at the end of the trajectory only
+            for (; l + (kRoomy ? 1 : 0) < L; ++l) {
+                if (!drifted) drift();
+                drifted = false;
+                ellp = eval<true, !kRoomy>(tg, c, pv, r, xp, gp);
+                kick();
+            }
+            if (kRoomy && l < L) {
+                if (!drifted) drift();
+                ellp = eval<true>(tg, c, pv, r, xp, gp);
+                kick();
             }
             double kin1 = 0.0, dle = 0.0;
 #pragma unroll
@@ -930,6 +1009,7 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
                 lw = 0.0;
                 accw = 0;
             }
+            int wait = 0;  // see look_in_vain
             const int tb = a.t_begin;
             const int te = a.t_end > 0 ? a.t_end : T;
             for (int t = tb + 1; t <= te; ++t) {
@@ -949,7 +1029,7 @@ __device__ __forceinline__ void oais_slot(const SweepArgs& a, const ParView& pv,
                 lw += lg;
                 const bool acc = Particle<FAM, LPP, DPL>::template move<MOVE>(
                     a.tg, c, pv, a.key, n, (uint32_t)t, r, a.leapfrog, a.beta[t], a.eps[t - 1], x,
-                    ell, g);
+                    ell, g, -1, &wait);
                 const uint64_t bal = __ballot(valid && acc && r == 0);
                 if (lane == 0) cntb[tc] = (uint32_t)__popcll(bal);
                 accw |= (acc ? 1u : 0u) << ((t - 1) & 31);
@@ -1066,6 +1146,7 @@ __global__ void __launch_bounds__(256) k_asmc_init(SweepArgs a, AsmcState z)
         (int64_t)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t n64 = tile * P + pl;
     if (tile >= a.ntiles || n64 >= a.N) return;
+    if (lane == 0) z.tile_part[(size_t)tile * 8 + 6] = 0.0;
     float x[DPL];
     double g[DPL];
     const double ell = Particle<FAM, LPP, DPL>::init(a.tg, c, pv, a.key, (uint32_t)n64, r, x, g,
@@ -1249,11 +1330,17 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
             // a rejected proposal's state is still in memory: neither it nor its
             // gradient is held over the step, and it is written only where it
             // comes from the gathered copies
+            constexpr bool kLooks = FAM == kGmm && MOVE == kHmc && LPP > 1;
+            int wait = 0;  // kept with the tile from step to step
+            if constexpr (kLooks)
+                wait = __builtin_amdgcn_readfirstlane((int)z.tile_part[(size_t)tile * 8 + 6]);
             float xp[DPL];
             double gp[DPL], ellp;
             acc = Particle<FAM, LPP, DPL>::template propose<MOVE>(a.tg, c, pv, a.key, (uint32_t)nl,
                                                                   (uint32_t)t, r, a.leapfrog, beta, eps,
-                                                                  x, ell, g, xp, ellp, gp);
+                                                                  x, ell, g, xp, ellp, gp, -1, &wait);
+            if constexpr (kLooks)
+                if (lane == 0) z.tile_part[(size_t)tile * 8 + 6] = (double)wait;
             if (acc) ell = ellp;
             if (rs && !acc) {
                 load_row<DPL>(Xs, nl, d, r, xp);
@@ -1328,10 +1415,11 @@ __global__ void __launch_bounds__(256) k_rejuv(RejuvArgs R)
 #pragma unroll
     for (int j = 0; j < DPL; ++j) s1[j] = s2[j] = 0.0;
     uint32_t na = 0;
+    int wait = 0;
     for (int s = 1; s <= a.T; ++s) {
         const bool acc = Particle<FAM, LPP, DPL>::template move<MOVE>(
             a.tg, c, pv, a.key, (uint32_t)n64, (uint32_t)(a.T + s), r, a.leapfrog, 1.0, R.eps, x,
-            ell, g);
+            ell, g, -1, &wait);
         na += acc ? 1u : 0u;
 #pragma unroll
         for (int j = 0; j < DPL; ++j) {
@@ -1432,11 +1520,13 @@ __global__ void __launch_bounds__(kPtMaxThreads) k_pt(PtArgs A)
     for (int j = 0; j < DPL; ++j) f1[j] = f2[j] = 0.0;
     double sm = -INFINITY, ss = 0.0;  // stepping stone of temperature tid (tid < Np)
     double trips = 0.0;               // round trips of replica tid (tid < R)
+    int wait = 0;
     __syncthreads();
     for (int t = 1; t <= a.T; ++t) {
         const int n = live ? tau[slot] : 0;
         Particle<FAM, LPP, DPL>::template move<MOVE>(a.tg, c, pv, a.key, gid, (uint32_t)t, r,
-                                                     a.leapfrog, A.beta[n], A.eps[n], x, ell, g);
+                                                     a.leapfrog, A.beta[n], A.eps[n], x, ell, g, -1,
+                                                     &wait);
         if (live && r == 0) Lsh[slot] = ell;
         __syncthreads();
         // swaps of the pairs (n, n + 1), n of the parity of t
