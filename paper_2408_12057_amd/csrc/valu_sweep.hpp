@@ -115,6 +115,18 @@ __device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char*
 }
 
 
+// Trajectories of a tile that go without looking for near components: none while
+// looking finds few, then 1, 3, 7 and at most 15 after each look in vain (the
+// number left in the low four bits, the last length above them).  A look costs
+// about a third of an evaluation.  Mixtures of 8 components at d = 100, 24 steps of 5
+// leapfrog steps, N = 20011: overlapping 1.49 ms without looking, 1.59 with a look a
+// trajectory, 1.53 so; far apart 1.56, 0.85 and 0.87.
+__device__ __forceinline__ int look_in_vain(int wait)
+{
+    const int n = min(2 * (wait >> 4) + 1, 15);
+    return (n << 4) | n;
+}
+
 // ---------------------------------------------------------------------------
 // Particle arithmetic for one lane group.
 // ---------------------------------------------------------------------------
@@ -122,26 +134,12 @@ __device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char*
 // exact zeros in x, z, the momentum and the gradient, and the lane-layout
 // means are zero there too, so every coordinate loop runs without a branch:
 // a padded coordinate adds +0 to each sum and stays +0 through every move.
-// Trajectories of a tile that go without looking for near components: none while
-// looking finds few, then 1, 3, 7 and at most 15 after each look in vain (the
-// number left in the low four bits, the last length above them).  A look costs
-// about a third of an evaluation.  Mixtures of 8 components at d = 100, 24 steps of 5
-// leapfrog steps, N = 20011: overlapping 1.49 ms without looking, 1.56 with a look a
-// trajectory, 1.51 so; far apart 1.58, 0.87 and 0.87.
-__device__ __forceinline__ int look_in_vain(int wait)
-{
-    const int n = min(2 * (wait >> 4) + 1, 15);
-    return (n << 4) | n;
-}
-
 template <int FAM, int LPP, int DPL>
 struct Particle {
-    // A mixture over lanes of 16 coordinates has no registers left in a trajectory:
-    // coordinates are then converted where they are used, components taken one by one
-    // and ell formed at every evaluation (24 HMC steps of 70000 overlapping particles at
-    // d = 30: 1.97 ms otherwise, 1.53 so; with 8 coordinates a lane, d = 100 and
-    // N = 20011, 1.56 so and 1.51 otherwise).
-    static constexpr bool kRoomy = FAM != kGmm || LPP == 1 || DPL <= 8;
+    static constexpr bool kLooks = FAM == kGmm && LPP > 1;  // HMC looks for near components
+    // Mixtures over lanes of 16 coordinates have no registers left in a trajectory, see
+    // mixture_multilane.
+    static constexpr bool kRoomy = !kLooks || DPL <= 8;
 
     // reference mean and target mean k at this lane's coordinate j
     static __device__ __forceinline__ double ref(const ParView& pv, int r, int j)
@@ -173,22 +171,22 @@ struct Particle {
         return x[0] > 0.f && (double)x[0] < tg.box && x[1] > 0.f && (double)x[1] < tg.box;
     }
 
-    // The coordinates in binary64, behind an empty asm: converted once and kept, where
-    // the compiler would convert them again at each component (a third of a
-    // component's instructions in the trajectories of a mixture over lanes).
+    // The coordinates in binary64; in the flat evaluation, where a lane has the
+    // registers, behind an empty asm: converted once and kept, where the compiler would
+    // convert them again at each component.
+    template <bool FLAT>
     static __device__ __forceinline__ void widen(const float (&x)[DPL], double (&xd)[DPL])
     {
 #pragma unroll
         for (int j = 0; j < DPL; ++j) {
             xd[j] = (double)x[j];
-            if constexpr (kRoomy) asm("" : "+v"(xd[j]));
+            if constexpr (FLAT && kRoomy) asm("" : "+v"(xd[j]));
         }
     }
 
     // |x - m_ref|^2 over the particle's lanes.
     template <typename X>
-    static __device__ __forceinline__ double ref_square(const ParView& pv, int r,
-                                                        const X (&x)[DPL])
+    static __device__ __forceinline__ double ref_square(const ParView& pv, int r, const X (&x)[DPL])
     {
         double sse = 0.0;
 #pragma unroll
@@ -201,13 +199,17 @@ struct Particle {
 
     // ell(x) = log gamma(x) - log eta(x); with GRAD also its gradient on this
     // lane's coordinates.  r = lane index inside the group.
-    // VALUE: whether ell itself is wanted (else 0 may come back): within a trajectory
+    // few (mixtures over several lanes): in, whether to look for the components
+    // that matter; out, whether they were few.
+    // value: whether ell itself is wanted (else 0 comes back: within a trajectory
     // only the gradient is, and the sums over the lanes and the logarithm are not
-    // formed.
-    template <bool GRAD, bool VALUE = true>
+    // formed).
+    // FLAT: see mixture_multilane.
+    template <bool GRAD, bool FLAT = false>
     static __device__ __forceinline__ double eval(const TargetDev& tg, const Consts& c,
                                                   const ParView& pv0, int r, const float (&x)[DPL],
-                                                  double (&g)[DPL])
+                                                  double (&g)[DPL], bool* few = nullptr,
+                                                  bool value = true)
     {
         const ParView pv = fresh(pv0);
         if constexpr (FAM == kUnid) {
@@ -226,7 +228,7 @@ struct Particle {
             return k * log1p((u - p) / p) + (n - k) * log1p(-(u - p) / (1.0 - p));
         } else if constexpr (FAM == kGauss) {
             double ssg = 0.0, sse = 0.0;
-            if constexpr (GRAD && !VALUE) {
+            if (GRAD && !value) {
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
                     const double xv = (double)x[j];
@@ -251,11 +253,14 @@ struct Particle {
             // equal-weight mixture of unnormalised isotropic components, streamed
             // over k with a running maximum (log-sum-exp and responsibilities)
             if constexpr (LPP > 1) {
-                double xd[DPL];
-                widen(x, xd);
-                return mixture_multilane<GRAD, VALUE>(tg, c, pv, r, xd, g);
+                if constexpr (GRAD) {
+                    uint32_t near;
+                    if (few && *few && (*few = near_components(tg, pv, r, x, near)))
+                        return mixture_few<FLAT>(tg, c, pv, r, x, g, near, value);
+                }
+                return mixture_multilane<GRAD, FLAT>(tg, c, pv, r, x, g, value);
             }
-            const double sse = VALUE ? ref_square(pv, r, x) : 0.0;
+            const double sse = value ? ref_square(pv, r, x) : 0.0;
 #pragma unroll
             for (int j = 0; j < DPL; ++j)
                 if (GRAD) g[j] = 0.0;
@@ -290,7 +295,7 @@ struct Particle {
                         g[j] = fma(f, mean(pv, k, r, j) - (double)x[j], g[j]);
                 }
             }
-            const double lse = VALUE ? mx + log(s) - c.logK : 0.0;
+            const double lse = value ? mx + log(s) - c.logK : 0.0;
             if (GRAD) {
                 const double inv_s = 1.0 / s;
 #pragma unroll
@@ -308,13 +313,23 @@ struct Particle {
     // log sum_k exp(e_k - M); the gradient gathers the weights from their
     // lanes.  (Streaming over k on every lane would repeat each exponential
     // LPP times.)
-    template <bool GRAD, bool VALUE>
+    // FLAT: the components' loops unrolled, and where a lane has the registers (8
+    // coordinates or fewer) the coordinates converted once instead of at each use and
+    // the gradient's components in whole blocks without branches.  For the
+    // trajectories of the sweeps, whose two waves per SIMD leave registers: 24 HMC steps
+    // of 5 leapfrog steps of 20011 overlapping particles, d = 100, 8 components, 1.78 ->
+    // 1.53 ms; 3 leapfrog steps of 70000 at d = 30, 2.04 -> 1.65 ms.  The per-step kernel's three
+    // waves spill (12.4 -> 15.1 ms for 96 steps of 65536 particles), and a MALA step,
+    // one evaluation, is 5 to 12% slower flat.
+    template <bool GRAD, bool FLAT>
     static __device__ __forceinline__ double mixture_multilane(const TargetDev& tg, const Consts& c,
                                                                const ParView& pv, int r,
-                                                               const double (&x)[DPL],
-                                                               double (&g)[DPL])
+                                                               const float (&x)[DPL],
+                                                               double (&g)[DPL], bool value)
     {
-        const double sse = VALUE ? ref_square(pv, r, x) : 0.0;
+        double xd[DPL];
+        widen<FLAT>(x, xd);
+        const double sse = value ? ref_square(pv, r, xd) : 0.0;
 #pragma unroll
         for (int j = 0; j < DPL; ++j)
             if (GRAD) g[j] = 0.0;
@@ -328,28 +343,35 @@ struct Particle {
         // interleave; the lane layout and 1/(2 v_k) are zero-padded to whole
         // blocks and a padded component gets e_k = -inf (weight 0)
         double M = -INFINITY;
+        auto block = [&](int k0) {
+            double sq[kKBlock];
 #pragma unroll
-        for (int k0 = 0; k0 < kMaxK; k0 += kKBlock) {
-            if (k0 < K) {
-                double sq[kKBlock];
+            for (int u = 0; u < kKBlock; ++u) {
+                sq[u] = 0.0;
 #pragma unroll
-                for (int u = 0; u < kKBlock; ++u) {
-                    sq[u] = 0.0;
-#pragma unroll
-                    for (int j = 0; j < DPL; ++j) {
-                        const double a = x[j] - mean(pv, k0 + u, r, j);
-                        sq[u] = fma(a, a, sq[u]);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kKBlock; ++u) {
-                    const int k = k0 + u;
-                    double ek = -group_sum<LPP>(sq[u]) * pv.hiv[k];
-                    if (k >= K) ek = -INFINITY;
-                    M = fmax(M, ek);
-                    if ((k % LPP) == r) eo[k / LPP] = ek;
+                for (int j = 0; j < DPL; ++j) {
+                    const double a = xd[j] - mean(pv, k0 + u, r, j);
+                    sq[u] = fma(a, a, sq[u]);
                 }
             }
+#pragma unroll
+            for (int u = 0; u < kKBlock; ++u) {
+                const int k = k0 + u;
+                double ek = -group_sum<LPP>(sq[u]) * pv.hiv[k];
+                if (k >= K) ek = -INFINITY;
+                M = fmax(M, ek);
+#pragma unroll
+                for (int q = 0; q < KO; ++q)
+                    if (k == q * LPP + r) eo[q] = ek;
+            }
+        };
+        if constexpr (FLAT) {
+#pragma unroll
+            for (int k0 = 0; k0 < kMaxK; k0 += kKBlock)
+                if (k0 < K) block(k0);
+        } else {
+#pragma unroll 1
+            for (int k0 = 0; k0 < K; k0 += kKBlock) block(k0);
         }
         double wo[KO];
         double so = 0.0;
@@ -359,32 +381,40 @@ struct Particle {
             so += wo[q];
         }
         const double s = group_sum<LPP>(so);
-        const double lse = VALUE ? M + log(s) - c.logK : 0.0;
+        const double lse = value ? M + log(s) - c.logK : 0.0;
         if (GRAD) {
             const int base = (int)(threadIdx.x & (kWave - 1)) & ~(LPP - 1);
             auto pull = [&](int k) {
-                const double f = __shfl(wo[k / LPP], base + k % LPP, kWave) * pv.iv[k];
+                double w = wo[0];
+#pragma unroll
+                for (int q = 1; q < KO; ++q) w = (k / LPP == q) ? wo[q] : w;
+                const double f = __shfl(w, base + k % LPP, kWave) * pv.iv[k];
 #pragma unroll
                 for (int j = 0; j < DPL; ++j)
-                    g[j] = fma(f, mean(pv, k, r, j) - x[j], g[j]);
+                    g[j] = fma(f, mean(pv, k, r, j) - xd[j], g[j]);
             };
-            // where there are registers for it whole blocks without a branch inside,
-            // as above, and the rest one by one
+            int k1 = 0;  // components taken
+            if constexpr (FLAT && kRoomy) {
 #pragma unroll
-            for (int k0 = 0; k0 < kMaxK; k0 += kKBlock) {
-                if (kRoomy && k0 + kKBlock <= K) {
+                for (int k0 = 0; k0 < kMaxK; k0 += kKBlock)
+                    if (k0 + kKBlock <= K) {
 #pragma unroll
-                    for (int u = 0; u < kKBlock; ++u) pull(k0 + u);
-                } else {
+                        for (int u = 0; u < kKBlock; ++u) pull(k0 + u);
+                    }
+                k1 = K / kKBlock * kKBlock;
+            }
+            if constexpr (FLAT && !kRoomy) {
 #pragma unroll
-                    for (int u = 0; u < (kRoomy ? kKBlock - 1 : kKBlock); ++u)
-                        if (k0 + u < K) pull(k0 + u);
-                }
+                for (int k = 0; k < kMaxK; ++k)
+                    if (k < K) pull(k);
+            } else {
+#pragma unroll 1
+                for (int k = k1; k < K; ++k) pull(k);
             }
             const double inv_s = 1.0 / s;
 #pragma unroll
             for (int j = 0; j < DPL; ++j)
-                g[j] = g[j] * inv_s + (x[j] - ref(pv, r, j)) * c.inv_s2r;
+                g[j] = g[j] * inv_s + (xd[j] - ref(pv, r, j)) * c.inv_s2r;
         }
         return lse + sse * c.half_inv_s2r + c.cst_eta;
     }
@@ -399,8 +429,8 @@ struct Particle {
     // component whose distance or exponent is not finite in binary32 is kept.  False
     // when some particle of the wave has more than half the components near, or three
     // eighths on two lanes a particle, where 32 particles share the walk (4 of 8 near,
-    // 24 steps: d = 30, N = 70000 1.95 ms by the walk and 1.53 all at once, d = 100,
-    // N = 20011 1.43 and 1.49).
+    // 24 steps: d = 30, N = 70000 1.93 ms by the walk and 1.65 all at once, d = 100,
+    // N = 20011 1.43 and 1.48).
     static __device__ __forceinline__ bool near_components(const TargetDev& tg, const ParView& pv,
                                                            int r, const float (&x)[DPL],
                                                            uint32_t& near)
@@ -482,14 +512,15 @@ struct Particle {
     // instead of 496 (96 HMC steps of 20011 particles: 6.20 -> 3.93 ms, of which
     // 4.44 -> 3.93 come from ell formed at a trajectory's end only, one force an
     // evaluation and the reduction of near_components).
+    template <bool FLAT>
     static __device__ __forceinline__ double mixture_few(const TargetDev& tg, const Consts& c,
                                                          const ParView& pv, int r,
-                                                         const float (&xf)[DPL], double (&g)[DPL],
+                                                         const float (&x)[DPL], double (&g)[DPL],
                                                          uint32_t near, bool value)
     {
-        double x[DPL];
-        widen(xf, x);
-        const double sse = value ? ref_square(pv, r, x) : 0.0;
+        double xd[DPL];
+        widen<FLAT>(x, xd);
+        const double sse = value ? ref_square(pv, r, xd) : 0.0;
 #pragma unroll
         for (int j = 0; j < DPL; ++j) g[j] = 0.0;
         constexpr int KO = (kMaxK + LPP - 1) / LPP;
@@ -505,7 +536,7 @@ struct Particle {
                 double sq = 0.0;
 #pragma unroll
                 for (int j = 0; j < DPL; ++j) {
-                    const double a = x[j] - mean(pv, k, r, j);
+                    const double a = xd[j] - mean(pv, k, r, j);
                     sq = fma(a, a, sq);
                 }
                 double ek = -group_sum<LPP>(sq) * pv.hiv[k];
@@ -515,8 +546,8 @@ struct Particle {
             const double f = pv.iv[k];
 #pragma unroll
             for (int j = 0; j < DPL; ++j) {
-                g[j] = fma(f, mean(pv, k, r, j) - x[j], g[j]);
-                g[j] = g[j] * inv_s + (x[j] - ref(pv, r, j)) * c.inv_s2r;
+                g[j] = fma(f, mean(pv, k, r, j) - xd[j], g[j]);
+                g[j] = g[j] * inv_s + (xd[j] - ref(pv, r, j)) * c.inv_s2r;
             }
             return lse + sse * c.half_inv_s2r + c.cst_eta;
         }
@@ -530,7 +561,7 @@ struct Particle {
             double sq = 0.0;
 #pragma unroll
             for (int j = 0; j < DPL; ++j) {
-                const double a = x[j] - mean(pv, k, r, j);
+                const double a = xd[j] - mean(pv, k, r, j);
                 sq = fma(a, a, sq);
             }
             const double ek = -group_sum<LPP>(sq) * pv.hiv[k];
@@ -562,13 +593,13 @@ struct Particle {
             const double f = __shfl(w, base + k % LPP, kWave) * pv.iv[k];
             if (on) {
 #pragma unroll
-                for (int j = 0; j < DPL; ++j) g[j] = fma(f, mean(pv, k, r, j) - x[j], g[j]);
+                for (int j = 0; j < DPL; ++j) g[j] = fma(f, mean(pv, k, r, j) - xd[j], g[j]);
             }
         }
         const double inv_s = 1.0 / s;
 #pragma unroll
         for (int j = 0; j < DPL; ++j)
-            g[j] = g[j] * inv_s + (x[j] - ref(pv, r, j)) * c.inv_s2r;
+            g[j] = g[j] * inv_s + (xd[j] - ref(pv, r, j)) * c.inv_s2r;
         return lse + sse * c.half_inv_s2r + c.cst_eta;
     }
 
@@ -721,7 +752,9 @@ struct Particle {
     // The proposal of one step and its accept decision, the state as it was: what
     // becomes of both is the caller's (grad ell of a state that lies in memory is
     // dead here after the first half step).
-    template <int MOVE>
+    // wait (HMC, mixtures over lanes): see look_in_vain; FLAT: the sweeps, see
+    // mixture_multilane.
+    template <int MOVE, bool FLAT = true>
     static __device__ __forceinline__ bool propose(const TargetDev& tg, const Consts& c,
                                                    const ParView& pv, const RngKey& key, uint32_t n,
                                                    uint32_t t, int r, int L, double beta, double eps,
@@ -808,37 +841,55 @@ struct Particle {
                     mom[j] += he * force[j];
                 }
             };
+            // the first evaluation of a trajectory looks for the components near
+            // its particles; the others do where that found few
+            const bool look = kLooks && pv.lmf && tg.K > 1 && (!wait || (*wait & 15) == 0);
             int l = 0;
-            bool drifted = false;  // the position of step l is there already
-            if constexpr (FAM == kGmm && LPP > 1) {
-                if (pv.lmf && tg.K > 1 && (!wait || (*wait & 15) == 0)) {
-                    for (; l < L && !drifted; l += drifted ? 0 : 1) {
+            bool vain = false;
+            if constexpr (!FLAT) {
+                bool few = look;
+                for (; l < L; ++l) {
+                    drift();
+                    ellp = eval<true>(tg, c, pv, r, xp, gp, &few, l + 1 == L);
+                    kick();
+                    if (l == 0) vain = look && !few;
+                }
+            } else {
+                bool drifted = false;  // the position of step l is there already
+                if constexpr (kLooks) {
+                    while (look && l < L && !drifted) {
                         drift();
                         const ParView pf = fresh(pv);
                         uint32_t near;
                         if (near_components(tg, pf, r, xp, near)) {
-                            ellp = mixture_few(tg, c, pf, r, xp, gp, near, l + 1 == L);
+                            ellp = mixture_few<true>(tg, c, pf, r, xp, gp, near, l + 1 == L);
                             kick();
+                            ++l;
                         } else {
                             drifted = true;
                         }
                     }
-                    if (wait) *wait = (drifted && l == 0) ? look_in_vain(*wait) : 0;
-                } else if (wait && (*wait & 15)) {
-                    --*wait;
+                    vain = drifted && l == 0;
+                }
+                // ell is wanted at the end only (without registers for a second copy
+                // of the evaluation it is formed each time)
+                for (; l + (kRoomy ? 1 : 0) < L; ++l) {
+                    if (!drifted) drift();
+                    drifted = false;
+                    ellp = eval<true, true>(tg, c, pv, r, xp, gp, nullptr, !kRoomy);
+                    kick();
+                }
+                if (kRoomy && l < L) {
+                    if (!drifted) drift();
+                    ellp = eval<true, true>(tg, c, pv, r, xp, gp);
+                    kick();
                 }
             }
-            // ell is wanted at the end of the trajectory only
-            for (; l + (kRoomy ? 1 : 0) < L; ++l) {
-                if (!drifted) drift();
-                drifted = false;
-                ellp = eval<true, !kRoomy>(tg, c, pv, r, xp, gp);
-                kick();
-            }
-            if (kRoomy && l < L) {
-                if (!drifted) drift();
-                ellp = eval<true>(tg, c, pv, r, xp, gp);
-                kick();
+            if (wait) {
+                if (look)
+                    *wait = vain ? look_in_vain(*wait) : 0;
+                else if (*wait & 15)
+                    --*wait;
             }
             double kin1 = 0.0, dle = 0.0;
 #pragma unroll
@@ -1330,13 +1381,13 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
             // a rejected proposal's state is still in memory: neither it nor its
             // gradient is held over the step, and it is written only where it
             // comes from the gathered copies
-            constexpr bool kLooks = FAM == kGmm && MOVE == kHmc && LPP > 1;
+            constexpr bool kLooks = MOVE == kHmc && Particle<FAM, LPP, DPL>::kLooks;
             int wait = 0;  // kept with the tile from step to step
             if constexpr (kLooks)
                 wait = __builtin_amdgcn_readfirstlane((int)z.tile_part[(size_t)tile * 8 + 6]);
             float xp[DPL];
             double gp[DPL], ellp;
-            acc = Particle<FAM, LPP, DPL>::template propose<MOVE>(a.tg, c, pv, a.key, (uint32_t)nl,
+            acc = Particle<FAM, LPP, DPL>::template propose<MOVE, (DPL > 8)>(a.tg, c, pv, a.key, (uint32_t)nl,
                                                                   (uint32_t)t, r, a.leapfrog, beta, eps,
                                                                   x, ell, g, xp, ellp, gp, -1, &wait);
             if constexpr (kLooks)
