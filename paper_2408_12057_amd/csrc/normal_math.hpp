@@ -3,18 +3,21 @@
 //
 // The sweeps are bound by VALU issue, and the library's log, sqrt and sincospi
 // were most of it: 124 binary64 and 70 other instructions a pair of normals
-// against 48 and 50 here.  The arguments make the difference: a uniform is a
+// against 51 and 50 here.  The arguments make the difference: a uniform is a
 // 32-bit integer plus 1/2 over 2^32, so nothing is zero, subnormal, infinite or
-// NaN, reductions are exact, and a table in LDS (4 KB) takes what a long
-// polynomial would.  Against 64-bit-mantissa references over 2^24 random words
-// and the extreme ones, errors in units in the last place (largest / root mean
-// square): log 0.57 / 0.288 (the library's 0.64 / 0.291), sine and cosine
-// 1.49 / 0.296 (0.88 / 0.302), the normals 2.97 / 0.537 (2.54 / 0.540).  The d = 10
-// Gaussian sweep of 2^22 particles and 64 steps: 13.15 -> 9.15 ms.
+// NaN, reductions are exact, and accurate tables in LDS (4.5 KB; points moved to
+// where the tabulated values lie close to binary64 numbers, S. Gal 1986) take what
+// a long polynomial would.  On the GPU against 64-bit-mantissa references over 2^23
+// random words, as many near the axes of the circle and the extreme ones, errors in
+// units in the last place (largest / root mean square over the random words):
+// -2 log 0.570 / 0.289 (the library's 0.641 / 0.292), sine and cosine 0.632 / 0.290
+// (0.884 / 0.301), the normals 2.38 / 0.533 (2.65 / 0.539).  The d = 10 Gaussian
+// sweep of 2^22 particles and 64 steps: 13.15 -> 9.15 ms when they came in, and later
+// 7.67 -> 7.77 ms for the closer sine and cosine below.
 //   * log: u = m 2^k, c near 1 / m with at most 29 bits, so that r = m c - 1 is
 //     exact, and -2 log u = -2 k log 2 + h + (-2 log(1 + r)) with h = 2 log c
 //     (plus 2 log 2 where the octave counts up) stored to 2^-44: each c was
-//     searched near 1 / m so that h lies within 2^-58 of such a multiple (2^-61
+//     searched near 1 / m so that h lies within 2^-57 of such a multiple (2^-60
 //     in the upper half octave), which makes the sum with the multiple of 2 log 2 exact.
 //     The last entry is c = 1/2, h = 0: near u = 1 the result is the series alone.
 //     |r| < 2^-7.9, Taylor series to r^7.
@@ -22,9 +25,13 @@
 //     the scaling that arguments beyond 2^+-767 would need.
 //   * sin and cos of 2 pi u: the nearest of 128 points of the circle, each displaced
 //     by a few 2^-32 turns to where its sine and cosine both lie within 0.006 units
-//     in the last place of binary64 numbers; then the remaining angle (|x| < pi / 127,
-//     from an exact integer difference) by Taylor series to x^7 and x^6, joined by
-//     the addition theorems.
+//     in the last place of binary64 numbers; then the remaining angle x, from an exact
+//     integer difference, by Taylor series to x^9 and x^8, joined by the addition
+//     theorems.  sin x enters as x and the rest, each multiplied by itself, so that
+//     its rounding does not enter; and the points next to an axis stand at the axis
+//     (|x| < 0.074 there, 0.025 elsewhere), where the small one of the two would
+//     otherwise be a difference of terms as large as itself.  (Rounding sin x and
+//     keeping those points had left 1.48 units.)
 #pragma once
 #include "device_common.hpp"
 
@@ -104,25 +111,25 @@ __device__ const double2 kLogTable[kLogEntries] = {
 // The circle's points: displacements from i / 128 of a turn in units of 2^-32 turns,
 // and {sin, cos} there
 __device__ const int32_t kCircleOffset[kCircle] = {
-    0, -941, 8596, 5965, -249, 17459, 82, 109,
+    0, -33554432, 8596, 5965, -249, 17459, 82, 109,
     5076, -1018, -3533, 1803, -9185, -9660, -15705, -5729,
     -2838, 5729, 15705, 9660, 9185, -1803, 3533, 1018,
-    -5076, -109, -82, -17459, 249, -5965, -8596, 941,
-    0, -941, 8596, 5965, -249, 17459, 82, 109,
+    -5076, -109, -82, -17459, 249, -5965, -8596, 33554432,
+    0, -33554432, 8596, 5965, -249, 17459, 82, 109,
     5076, -1018, -3533, 1803, -9185, -9660, -15705, -5729,
     2838, 5729, 15705, 9660, 9185, -1803, 3533, 1018,
-    -5076, -109, -82, -17459, 249, -5965, -8596, 941,
-    0, -941, 8596, 5965, -249, 17459, 82, 109,
+    -5076, -109, -82, -17459, 249, -5965, -8596, 33554432,
+    0, -33554432, 8596, 5965, -249, 17459, 82, 109,
     5076, -1018, -3533, 1803, -9185, -9660, -15705, -5729,
     -2838, 5729, 15705, 9660, 9185, -1803, 3533, 1018,
-    -5076, -109, -82, -17459, 249, -5965, -8596, 941,
-    0, -941, 8596, 5965, -249, 17459, 82, 109,
+    -5076, -109, -82, -17459, 249, -5965, -8596, 33554432,
+    0, -33554432, 8596, 5965, -249, 17459, 82, 109,
     5076, -1018, -3533, 1803, -9185, -9660, -15705, -5729,
     2838, 5729, 15705, 9660, 9185, -1803, 3533, 1018,
-    -5076, -109, -82, -17459, 249, -5965, -8596, 941,
+    -5076, -109, -82, -17459, 249, -5965, -8596, 33554432,
 };
 __device__ const double2 kCircleTable[kCircle] = {
-    {0x0.0p+0, 0x1.0000000000000p+0}, {0x1.91f37ce57b513p-5, 0x1.ff62207bcddb8p-1},
+    {0x0.0p+0, 0x1.0000000000000p+0}, {0x0.0p+0, 0x1.0000000000000p+0},
     {0x1.91878b250fc49p-4, 0x1.fd88b0e08872fp-1}, {0x1.2c858d751049ap-3, 0x1.fa752cf988fb9p-1},
     {0x1.8f8b53d2fdac6p-3, 0x1.f6297f61e6fe2p-1}, {0x1.f1ac95044bda9p-3, 0x1.f0a71f7979aa5p-1},
     {0x1.29406aa17ebc6p-2, 0x1.e9f4144143b63p-1}, {0x1.58f9b16e069a3p-2, 0x1.e2120e81f54d4p-1},
@@ -137,8 +144,8 @@ __device__ const double2 kCircleTable[kCircle] = {
     {0x1.d9065d98c07d3p-1, 0x1.87dff6d18d7d2p-2}, {0x1.e2120e81f54d4p-1, 0x1.58f9b16e069a3p-2},
     {0x1.e9f4144143b63p-1, 0x1.29406aa17ebc6p-2}, {0x1.f0a71f7979aa5p-1, 0x1.f1ac95044bda9p-3},
     {0x1.f6297f61e6fe2p-1, 0x1.8f8b53d2fdac6p-3}, {0x1.fa752cf988fb9p-1, 0x1.2c858d751049ap-3},
-    {0x1.fd88b0e08872fp-1, 0x1.91878b250fc49p-4}, {0x1.ff62207bcddb8p-1, 0x1.91f37ce57b513p-5},
-    {0x1.0000000000000p+0, 0x0.0p+0}, {0x1.ff62207bcddb8p-1, -0x1.91f37ce57b513p-5},
+    {0x1.fd88b0e08872fp-1, 0x1.91878b250fc49p-4}, {0x1.0000000000000p+0, 0x0.0p+0},
+    {0x1.0000000000000p+0, 0x0.0p+0}, {0x1.0000000000000p+0, 0x0.0p+0},
     {0x1.fd88b0e08872fp-1, -0x1.91878b250fc49p-4}, {0x1.fa752cf988fb9p-1, -0x1.2c858d751049ap-3},
     {0x1.f6297f61e6fe2p-1, -0x1.8f8b53d2fdac6p-3}, {0x1.f0a71f7979aa5p-1, -0x1.f1ac95044bda9p-3},
     {0x1.e9f4144143b63p-1, -0x1.29406aa17ebc6p-2}, {0x1.e2120e81f54d4p-1, -0x1.58f9b16e069a3p-2},
@@ -153,8 +160,8 @@ __device__ const double2 kCircleTable[kCircle] = {
     {0x1.87dff6d18d7d2p-2, -0x1.d9065d98c07d3p-1}, {0x1.58f9b16e069a3p-2, -0x1.e2120e81f54d4p-1},
     {0x1.29406aa17ebc6p-2, -0x1.e9f4144143b63p-1}, {0x1.f1ac95044bda9p-3, -0x1.f0a71f7979aa5p-1},
     {0x1.8f8b53d2fdac6p-3, -0x1.f6297f61e6fe2p-1}, {0x1.2c858d751049ap-3, -0x1.fa752cf988fb9p-1},
-    {0x1.91878b250fc49p-4, -0x1.fd88b0e08872fp-1}, {0x1.91f37ce57b513p-5, -0x1.ff62207bcddb8p-1},
-    {0x0.0p+0, -0x1.0000000000000p+0}, {-0x1.91f37ce57b513p-5, -0x1.ff62207bcddb8p-1},
+    {0x1.91878b250fc49p-4, -0x1.fd88b0e08872fp-1}, {0x0.0p+0, -0x1.0000000000000p+0},
+    {0x0.0p+0, -0x1.0000000000000p+0}, {0x0.0p+0, -0x1.0000000000000p+0},
     {-0x1.91878b250fc49p-4, -0x1.fd88b0e08872fp-1}, {-0x1.2c858d751049ap-3, -0x1.fa752cf988fb9p-1},
     {-0x1.8f8b53d2fdac6p-3, -0x1.f6297f61e6fe2p-1}, {-0x1.f1ac95044bda9p-3, -0x1.f0a71f7979aa5p-1},
     {-0x1.29406aa17ebc6p-2, -0x1.e9f4144143b63p-1}, {-0x1.58f9b16e069a3p-2, -0x1.e2120e81f54d4p-1},
@@ -169,8 +176,8 @@ __device__ const double2 kCircleTable[kCircle] = {
     {-0x1.d9065d98c07d3p-1, -0x1.87dff6d18d7d2p-2}, {-0x1.e2120e81f54d4p-1, -0x1.58f9b16e069a3p-2},
     {-0x1.e9f4144143b63p-1, -0x1.29406aa17ebc6p-2}, {-0x1.f0a71f7979aa5p-1, -0x1.f1ac95044bda9p-3},
     {-0x1.f6297f61e6fe2p-1, -0x1.8f8b53d2fdac6p-3}, {-0x1.fa752cf988fb9p-1, -0x1.2c858d751049ap-3},
-    {-0x1.fd88b0e08872fp-1, -0x1.91878b250fc49p-4}, {-0x1.ff62207bcddb8p-1, -0x1.91f37ce57b513p-5},
-    {-0x1.0000000000000p+0, 0x0.0p+0}, {-0x1.ff62207bcddb8p-1, 0x1.91f37ce57b513p-5},
+    {-0x1.fd88b0e08872fp-1, -0x1.91878b250fc49p-4}, {-0x1.0000000000000p+0, 0x0.0p+0},
+    {-0x1.0000000000000p+0, 0x0.0p+0}, {-0x1.0000000000000p+0, 0x0.0p+0},
     {-0x1.fd88b0e08872fp-1, 0x1.91878b250fc49p-4}, {-0x1.fa752cf988fb9p-1, 0x1.2c858d751049ap-3},
     {-0x1.f6297f61e6fe2p-1, 0x1.8f8b53d2fdac6p-3}, {-0x1.f0a71f7979aa5p-1, 0x1.f1ac95044bda9p-3},
     {-0x1.e9f4144143b63p-1, 0x1.29406aa17ebc6p-2}, {-0x1.e2120e81f54d4p-1, 0x1.58f9b16e069a3p-2},
@@ -185,7 +192,7 @@ __device__ const double2 kCircleTable[kCircle] = {
     {-0x1.87dff6d18d7d2p-2, 0x1.d9065d98c07d3p-1}, {-0x1.58f9b16e069a3p-2, 0x1.e2120e81f54d4p-1},
     {-0x1.29406aa17ebc6p-2, 0x1.e9f4144143b63p-1}, {-0x1.f1ac95044bda9p-3, 0x1.f0a71f7979aa5p-1},
     {-0x1.8f8b53d2fdac6p-3, 0x1.f6297f61e6fe2p-1}, {-0x1.2c858d751049ap-3, 0x1.fa752cf988fb9p-1},
-    {-0x1.91878b250fc49p-4, 0x1.fd88b0e08872fp-1}, {-0x1.91f37ce57b513p-5, 0x1.ff62207bcddb8p-1},
+    {-0x1.91878b250fc49p-4, 0x1.fd88b0e08872fp-1}, {0x0.0p+0, 0x1.0000000000000p+0},
 };
 
 // The tables in LDS.
@@ -247,14 +254,18 @@ __device__ __forceinline__ void circle_word(const NormalTables& tb, uint32_t w, 
     const double d = (double)((int32_t)(w - (i << 25)) - tb.offset[i & (kCircle - 1)]) + 0.5;
     const double x = d * 0x1.921fb54442d18p-30;  // 2 pi 2^-32
     const double z = x * x;
-    const double sp = fma(fma(z, -1.0 / 5040.0, 1.0 / 120.0), z, -1.0 / 6.0);
-    const double cp = fma(fma(z, -1.0 / 720.0, 1.0 / 24.0), z, -1.0 / 2.0);
-    // sin x (with the low parts of the product and of 2 pi) and cos x - 1
+    double sp = fma(z, 1.0 / 362880.0, -1.0 / 5040.0);
+    double cp = fma(z, 1.0 / 40320.0, -1.0 / 720.0);
+    sp = fma(sp, z, 1.0 / 120.0);
+    cp = fma(cp, z, 1.0 / 24.0);
+    sp = fma(sp, z, -1.0 / 6.0);
+    cp = fma(cp, z, -1.0 / 2.0);
+    // sin x = x + sl (with the low parts of the product and of 2 pi), cos x - 1 = cm
     const double lo = fma(d, 0x1.1a62633145c07p-84, fma(d, 0x1.921fb54442d18p-30, -x));
-    const double sx = x + fma(x * z, sp, lo);
+    const double sl = fma(x * z, sp, lo);
     const double cm = z * cp;
-    s = t.x + fma(t.y, sx, t.x * cm);
-    c = t.y + fma(-t.x, sx, t.y * cm);
+    s = t.x + fma(t.y, x, fma(t.y, sl, t.x * cm));
+    c = t.y + fma(-t.x, x, fma(-t.x, sl, t.y * cm));
 }
 
 // Box-Muller: (wa, wb) -> (r cos 2 pi u_b, r sin 2 pi u_b), r = sqrt(-2 log u_a).
