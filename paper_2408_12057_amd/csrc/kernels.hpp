@@ -79,17 +79,18 @@ __host__ __device__ inline size_t lane_params_offset(const TargetDev& tg)
     return (2 * kMaxK * sizeof(double) + (size_t)(tg.d + nmu) * sizeof(float) + 7) & ~(size_t)7;
 }
 // Binary32 means of a mixture whose particles span lanes, a lane's coordinates
-// contiguous (16-byte reads), behind the binary64 ones.
-__host__ __device__ inline size_t lane_param_floats(const TargetDev& tg, int lpp, int dpl)
+// contiguous (16-byte reads), behind the binary64 ones; only HMC reads them.
+__host__ __device__ inline size_t lane_param_floats(const TargetDev& tg, int move, int lpp, int dpl)
 {
-    return (tg.family == kGmm && lpp > 1) ? (size_t)lane_means(tg) * lpp * dpl : 0;
+    return (tg.family == kGmm && move == kHmc && lpp > 1) ? (size_t)lane_means(tg) * lpp * dpl : 0;
 }
-// Dynamic LDS of a VALU kernel with the lane-layout parameters of a shape.
-__host__ __device__ inline size_t params_bytes_lanes(const TargetDev& tg, int lpp, int dpl)
+// Dynamic LDS of a VALU kernel with the lane-layout parameters of a move and shape (at
+// most 69 KB: HMC, 16 components at d = 256).
+__host__ __device__ inline size_t params_bytes_lanes(const TargetDev& tg, int move, int lpp, int dpl)
 {
     return ((lane_params_offset(tg) + 15) & ~(size_t)15) +
            lane_param_doubles(tg, lpp, dpl) * sizeof(double) +
-           lane_param_floats(tg, lpp, dpl) * sizeof(float);
+           lane_param_floats(tg, move, lpp, dpl) * sizeof(float);
 }
 
 // Arguments of one annealing pass.
@@ -220,6 +221,7 @@ struct ValuShape {
 
 // Lanes that fill every SIMD of the GPU twice (256 CUs x 4 SIMDs x 64 x 2).
 constexpr int64_t kFillCus = 256;
+constexpr size_t kLdsPerCu = 160 * 1024;
 constexpr int64_t kFillLanes = kFillCus * 4 * 64 * 2;
 bool valu_shape(int d, int64_t N, ValuShape* s);
 
@@ -271,11 +273,13 @@ hipError_t launch_target_eval(const EvalArgs& E, const ValuShape& s, hipStream_t
 __host__ __device__ inline size_t pt_shared_bytes(const PtArgs& A, int lpp, int dpl)
 {
     const size_t R = (size_t)A.Np + 1;
-    size_t off = params_bytes_lanes(A.a.tg, lpp, dpl);
+    size_t off = params_bytes_lanes(A.a.tg, A.a.move, lpp, dpl);
     off = (off + 15) & ~(size_t)15;
     return off + R * sizeof(double) + (size_t)A.Np * sizeof(double) + 3 * R * sizeof(int) +
            16 * sizeof(double);
 }
+// The tables of the normals beside it (static LDS of the kernels that draw).
+constexpr size_t kNormalTableBytes = 4608;
 hipError_t launch_pt_reduce(const PtArgs& A, const ValuShape& s, double* res, hipStream_t st);
 hipError_t launch_rejuv_reduce(const double* tsum, int64_t ntiles, int d, double samples,
                                double* out, hipStream_t st);
@@ -288,7 +292,7 @@ hipError_t launch_resample_event(int64_t N, const double* lw, const RngKey& key,
 // final log-weights in entry T): moments, accepted counts, the log Z_hat factor
 // and, when t_end < T, the resampling event (flag, largest log w, uniform word).
 hipError_t launch_segment_merge(const SweepArgs& a, const AsmcState& z, hipStream_t st);
-// ZJA (online CESS-adaptive AIS): beta_t by bisection of log CESS on the
+// ZJA (online CESS-adaptive AIS): beta_t from the crossing of log CESS on the
 // device (one workgroup), then the step's reweight and move without a merge;
 // log Z_hat from the final log-weights into logZ[0].
 hipError_t launch_zja_select(int64_t N, const double* lw, const double* ell, double* beta, int t,

@@ -1366,7 +1366,7 @@ int oasmc_pt(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel* 
     A.K = K;
     A.Np = Np;
     A.stride = 3 * (int64_t)Np + 2;
-    if (pt_shared_bytes(A, shape.lpp, shape.dpl) > h->lds_per_block)
+    if (pt_shared_bytes(A, shape.lpp, shape.dpl) + kNormalTableBytes > h->lds_per_block)
         return fail(OASMC_EUNSUPPORTED, "too many chains for the LDS of one workgroup");
     double *dbeta, *deps, *out, *fpart, *dres;
     const int nres = 2 * Np + 1 + 2 * d;

@@ -82,24 +82,18 @@ __device__ __forceinline__ ParView stage_params(const TargetDev& tg, char* sh)
     return ParView{m, mu, hv, iv, nullptr, nullptr, nullptr, nullptr};
 }
 
-inline size_t params_bytes(const TargetDev& tg)
-{
-    const int nmu = (tg.family == kGmm) ? tg.K * tg.d : tg.d;
-    return 2 * kMaxK * sizeof(double) + (size_t)(tg.d + nmu) * sizeof(float);
-}
-
 
 // The same staging followed by the binary64 lane-layout means lm, lmu of the
-// shape (LPP, DPL) and the tables of the normals.
-template <int LPP, int DPL>
-__device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char* sh, NormalTables& nt)
+// move's shape (LPP, DPL) and, for kernels that draw, the tables of the normals.
+template <int MOVE, int LPP, int DPL>
+__device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char* sh, NormalTables* nt)
 {
-    stage_tables(nt);
+    if (nt) stage_tables(*nt);
     const ParView base = stage_params(tg, sh);
     double* lane = reinterpret_cast<double*>(sh + ((lane_params_offset(tg) + 15) & ~(size_t)15));
     const int nl = (int)lane_param_doubles(tg, LPP, DPL);
     float* lmf = nullptr;
-    if (lane_param_floats(tg, LPP, DPL) > 0) lmf = reinterpret_cast<float*>(lane + nl);
+    if (lane_param_floats(tg, MOVE, LPP, DPL) > 0) lmf = reinterpret_cast<float*>(lane + nl);
     for (int e = threadIdx.x; e < nl; e += blockDim.x) {
         const double v = lane_param(tg, LPP, DPL, e);
         lane[e] = v;
@@ -111,7 +105,7 @@ __device__ __forceinline__ ParView stage_params_lanes(const TargetDev& tg, char*
         }
     }
     __syncthreads();
-    return ParView{base.m, base.mu, base.hiv, base.iv, lane, lane + LPP * DPL, &nt, lmf};
+    return ParView{base.m, base.mu, base.hiv, base.iv, lane, lane + LPP * DPL, nt, lmf};
 }
 
 
@@ -1131,7 +1125,7 @@ __global__ void __launch_bounds__(256, (SweepWaves<DPL>::value)) k_oais_valu(Swe
     __shared__ uint32_t sh_cnt[kWavesPerBlock][kTC];
     extern __shared__ __align__(16) char sh_dyn[];
     __shared__ NormalTables sh_nt;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
+    const ParView pv = stage_params_lanes<MOVE, LPP, DPL>(a.tg, sh_dyn, &sh_nt);
     const Consts c = make_consts(a.tg);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform
     const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + wv;
@@ -1189,7 +1183,7 @@ __global__ void __launch_bounds__(256) k_asmc_init(SweepArgs a, AsmcState z)
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
     __shared__ NormalTables sh_nt;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
+    const ParView pv = stage_params_lanes<MOVE, LPP, DPL>(a.tg, sh_dyn, &sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
@@ -1292,7 +1286,8 @@ __device__ __forceinline__ void store_row(double* __restrict__ p, int64_t row, i
 
 // The launch has at most as many blocks as are resident, and each walks over
 // tiles: the staging of the target's parameters and tables (a few us of dependent
-// loads) is paid once a block and not once a tile (the step above: 195 -> 142 us).
+// loads) is paid once a block and not once a tile (the d = 100, 8-component HMC step
+// of 65536 particles: 195 -> 142 us).
 template <int FAM, int MOVE, int LPP, int DPL>
 __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
     k_asmc_step(SweepArgs a, AsmcState z, int t)
@@ -1301,7 +1296,7 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
     __shared__ NormalTables sh_nt;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
+    const ParView pv = stage_params_lanes<MOVE, LPP, DPL>(a.tg, sh_dyn, &sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
@@ -1440,7 +1435,7 @@ __global__ void __launch_bounds__(256) k_rejuv(RejuvArgs R)
     extern __shared__ __align__(16) char sh_dyn[];
     const SweepArgs& a = R.a;
     __shared__ NormalTables sh_nt;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
+    const ParView pv = stage_params_lanes<MOVE, LPP, DPL>(a.tg, sh_dyn, &sh_nt);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
@@ -1537,11 +1532,11 @@ __global__ void __launch_bounds__(kPtMaxThreads) k_pt(PtArgs A)
     extern __shared__ __align__(16) char sh_dyn[];
     const SweepArgs& a = A.a;
     __shared__ NormalTables sh_nt;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
+    const ParView pv = stage_params_lanes<MOVE, LPP, DPL>(a.tg, sh_dyn, &sh_nt);
     const Consts c = make_consts(a.tg);
     const int R = A.Np + 1;
     const int Np = A.Np;
-    size_t off = (params_bytes_lanes(a.tg, LPP, DPL) + 15) & ~(size_t)15;
+    size_t off = (params_bytes_lanes(a.tg, MOVE, LPP, DPL) + 15) & ~(size_t)15;
     double* Lsh = reinterpret_cast<double*>(sh_dyn + off);   // [R] ell of replica r
     double* rsum = Lsh + R;                                   // [Np] summed rejections
     int* tau = reinterpret_cast<int*>(rsum + Np);             // [R] temperature of replica r
@@ -1674,8 +1669,7 @@ __global__ void __launch_bounds__(256) k_target_eval(EvalArgs E)
     constexpr int P = kWave / LPP;
     extern __shared__ __align__(16) char sh_dyn[];
     const SweepArgs& a = E.a;
-    __shared__ NormalTables sh_nt;
-    const ParView pv = stage_params_lanes<LPP, DPL>(a.tg, sh_dyn, sh_nt);
+    const ParView pv = stage_params_lanes<kMala, LPP, DPL>(a.tg, sh_dyn, nullptr);
     const Consts c = make_consts(a.tg);
     const int lane = threadIdx.x & (kWave - 1);
     const int r = lane % LPP, pl = lane / LPP;
@@ -1704,13 +1698,15 @@ __global__ void __launch_bounds__(256) k_target_eval(EvalArgs E)
     if (r == 0) E.ell[n64] = ell;
 }
 
+static_assert(sizeof(NormalTables) == kNormalTableBytes, "counted beside the dynamic LDS");
+
 template <int FAM, int MOVE, int LPP, int DPL>
 struct Launch {
     static hipError_t oais(const SweepArgs& a, int grid_waves, hipStream_t st)
     {
         const int blocks = (grid_waves + kWavesPerBlock - 1) / kWavesPerBlock;
         hipLaunchKernelGGL((k_oais_valu<FAM, MOVE, LPP, DPL>), dim3(blocks), dim3(256),
-                           params_bytes_lanes(a.tg, LPP, DPL), st, a);
+                           params_bytes_lanes(a.tg, MOVE, LPP, DPL), st, a);
         return hipGetLastError();
     }
     static hipError_t batch(const SweepArgs* args, const ParView* views, const int2* items,
@@ -1725,14 +1721,14 @@ struct Launch {
     {
         const int64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
         hipLaunchKernelGGL((k_asmc_init<FAM, MOVE, LPP, DPL>), dim3((unsigned)blocks), dim3(256),
-                           params_bytes_lanes(a.tg, LPP, DPL), st, a, z);
+                           params_bytes_lanes(a.tg, MOVE, LPP, DPL), st, a, z);
         return hipGetLastError();
     }
     static hipError_t rejuv(const RejuvArgs& R, hipStream_t st)
     {
         const int64_t blocks = (R.a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
         hipLaunchKernelGGL((k_rejuv<FAM, MOVE, LPP, DPL>), dim3((unsigned)blocks), dim3(256),
-                           params_bytes_lanes(R.a.tg, LPP, DPL), st, R);
+                           params_bytes_lanes(R.a.tg, MOVE, LPP, DPL), st, R);
         return hipGetLastError();
     }
     static hipError_t pt(const PtArgs& A, hipStream_t st)
@@ -1750,7 +1746,7 @@ struct Launch {
         if constexpr (MOVE == kMala || (FAM == kUnid && MOVE == kRwmh)) {
             const int64_t blocks = (E.a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
             hipLaunchKernelGGL((k_target_eval<FAM, LPP, DPL>), dim3((unsigned)blocks), dim3(256),
-                               params_bytes_lanes(E.a.tg, LPP, DPL), st, E);
+                               params_bytes_lanes(E.a.tg, kMala, LPP, DPL), st, E);
             return hipGetLastError();
         } else {
             (void)E;
@@ -1760,17 +1756,19 @@ struct Launch {
     }
     static hipError_t step(const SweepArgs& a, const AsmcState& z, int t, hipStream_t st)
     {
-        // resident blocks of this instantiation (a property of the kernel)
-        static const int per_cu = [] {
+        // resident blocks: as many as the registers of this instantiation and its LDS allow
+        static const int by_registers = [] {
             int n = 0;
             const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
                 &n, reinterpret_cast<const void*>(&k_asmc_step<FAM, MOVE, LPP, DPL>), 256, 0);
             return (e == hipSuccess && n > 0) ? n : 2;
         }();
+        const size_t lds = params_bytes_lanes(a.tg, MOVE, LPP, DPL);
+        const int per_cu = std::min<int>(by_registers, (int)(kLdsPerCu / (lds + sizeof(NormalTables))));
         const int64_t blocks = std::min<int64_t>((a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock,
                                                  (int64_t)kFillCus * per_cu);
         hipLaunchKernelGGL((k_asmc_step<FAM, MOVE, LPP, DPL>), dim3((unsigned)blocks), dim3(256),
-                           params_bytes_lanes(a.tg, LPP, DPL), st, a, z, t);
+                           lds, st, a, z, t);
         return hipGetLastError();
     }
 };
