@@ -1099,8 +1099,11 @@ hipError_t launch_zja_select(int64_t N, const double* lw, const double* ell, dou
                              hipStream_t st)
 {
     const size_t shb = sizeof(double2) * (size_t)std::min<int64_t>(N, kZjaHeld);
+    // the attribute belongs to the process: always the largest, whatever N, so that
+    // calls of several threads do not take LDS from each other
     const hipError_t e = hipFuncSetAttribute((const void*)k_zja_select,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shb);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)(sizeof(double2) * kZjaHeld));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_zja_select, dim3(1), dim3(kZjaThreads), shb, st, N, lw, ell, beta, t, Tmax,
                        log_rho, iters, stop, log_g);
