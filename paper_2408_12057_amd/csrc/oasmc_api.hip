@@ -54,11 +54,15 @@ void clear_error() { g_err.clear(); }
 
 namespace {
 
+// The failed call's error is reported here, and taken from the thread's last error, where
+// the next launch of this library or of torch would find it again.
 #define HIP_TRY(expr)                                                                   \
     do {                                                                                \
         hipError_t e_ = (expr);                                                         \
-        if (e_ != hipSuccess)                                                           \
+        if (e_ != hipSuccess) {                                                         \
+            (void)hipGetLastError();                                                    \
             return fail(OASMC_EHIP, "%s failed: %s", #expr, hipGetErrorString(e_));     \
+        }                                                                               \
     } while (0)
 
 // One growable device allocation.
@@ -1062,8 +1066,19 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
     const double* const scal = hout + 4 * (size_t)T;
     std::copy_n(beta, T + 1, hin);
     std::copy_n(eps, T, hin + T + 1);
+    // an error after the first copy waits for the stream: the handle's next call may
+    // refill or free the pinned buffer
+    struct Drain {
+        hipStream_t st;
+        bool on = false;
+        ~Drain()
+        {
+            if (on) (void)hipStreamSynchronize(st);
+        }
+    } drain{st};
     // (after a shape has been measured: its trial passes use the same buffer)
     auto send_schedule = [&] {
+        drain.on = true;
         return hipMemcpyAsync(dbeta, hin, sizeof(double) * nin, hipMemcpyHostToDevice, st);
     };
     a.beta = dbeta;
@@ -1109,6 +1124,7 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
         HIP_TRY(launch_merge_slots(part, S, T, N, dlogg, dacc, dscal, st));
         HIP_TRY(hipMemcpyAsync(hin + nin, dlogg, sizeof(double) * (4 * (size_t)T + 1), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
+        drain.on = false;
         std::copy_n(hout, 3 * (size_t)T, out->log_g);
         std::copy_n(hout + 3 * (size_t)T, T, out->accept);
         if (h->prof) {
@@ -1202,6 +1218,7 @@ int oasmc_asmc(oasmc_handle* h, const oasmc_problem* problem, const oasmc_kernel
         if (out->x)
             HIP_TRY(hipMemcpyAsync(out->x, z.X, sizeof(float) * N * d, hipMemcpyDeviceToDevice, st));
         HIP_TRY(hipStreamSynchronize(st));
+        drain.on = false;
         const int* const hres = reinterpret_cast<const int*>(scal + 8 + T);
         nres = hres[0];
         std::copy_n(hout, 3 * (size_t)T, out->log_g);
