@@ -26,7 +26,9 @@ FLAGS = [
 # registers a lane for the whole kernel, and what spills for them costs more than
 # the moves saved (a logistic-regression run 664 -> 648 ms, the d = 100 mixture
 # HMC step 155 -> 126 us, a d = 100 Gaussian MALA run 6.0 -> 4.4 ms).  The
-# other sources hold no such loop.
+# other sources hold no such loop.  The option is LLVM's own: a compiler without it
+# stops the build, and the waves per SIMD of the step kernels (MinWaves, SweepWaves)
+# were chosen with it, so they are to be measured again if it goes.
 IN_PLACE_CONSTANTS = ["-mllvm", "-disable-machine-licm"]
 IN_PLACE_SOURCES = ("valu_", "sweep_logreg", "adjoint")
 

@@ -1148,7 +1148,7 @@ __device__ __forceinline__ double block_sum(double v, double* shw)
 
 // Column b of the tile sums over tiles in a fixed order.  Bound by the latency of
 // the column's loads (a cache line each, few columns): a workgroup of 16 waves per
-// column has them in flight at once (2^19 particles at d = 10: 85 -> 22 us).
+// column has them in flight at once (2^20 particles at d = 10: 85 -> 22 us).
 constexpr int kColThreads = 1024;
 __global__ void __launch_bounds__(kColThreads) k_rejuv_reduce(const double* __restrict__ tsum,
                                                                int64_t ntiles, int d, double samples,

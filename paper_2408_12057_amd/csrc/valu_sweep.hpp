@@ -746,8 +746,10 @@ struct Particle {
     // The proposal of one step and its accept decision, the state as it was: what
     // becomes of both is the caller's (grad ell of a state that lies in memory is
     // dead here after the first half step).
-    // wait (HMC, mixtures over lanes): see look_in_vain; FLAT: the sweeps, see
-    // mixture_multilane.
+    // FLAT: the sweeps, see mixture_multilane.  wait (HMC, mixtures over lanes, FLAT):
+    // see look_in_vain; the other form looks every time (with a condition on its first
+    // look the step kernel keeps 30 scalar registers more in vector lanes, 3 % of its
+    // time).
     template <int MOVE, bool FLAT = true>
     static __device__ __forceinline__ bool propose(const TargetDev& tg, const Consts& c,
                                                    const ParView& pv, const RngKey& key, uint32_t n,
@@ -821,36 +823,42 @@ struct Particle {
 #pragma unroll
             for (int j = 0; j < DPL; ++j)
                 force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
-            auto drift = [&] {
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    mom[j] += he * force[j];
-                    xp[j] = (float)((double)xp[j] + eps * mom[j]);
-                }
-            };
-            auto kick = [&] {
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
-                    mom[j] += he * force[j];
-                }
-            };
             // the first evaluation of a trajectory looks for the components near
             // its particles; the others do where that found few
-            const bool look = kLooks && pv.lmf && tg.K > 1 && (!wait || (*wait & 15) == 0);
-            int l = 0;
-            bool vain = false;
             if constexpr (!FLAT) {
-                bool few = look;
-                for (; l < L; ++l) {
-                    drift();
+                bool few = pv.lmf != nullptr;
+                for (int l = 0; l < L; ++l) {
+#pragma unroll
+                    for (int j = 0; j < DPL; ++j) {
+                        mom[j] += he * force[j];
+                        xp[j] = (float)((double)xp[j] + eps * mom[j]);
+                    }
                     ellp = eval<true>(tg, c, pv, r, xp, gp, &few, l + 1 == L);
-                    kick();
-                    if (l == 0) vain = look && !few;
+#pragma unroll
+                    for (int j = 0; j < DPL; ++j) {
+                        force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
+                        mom[j] += he * force[j];
+                    }
                 }
             } else {
+                auto drift = [&] {
+#pragma unroll
+                    for (int j = 0; j < DPL; ++j) {
+                        mom[j] += he * force[j];
+                        xp[j] = (float)((double)xp[j] + eps * mom[j]);
+                    }
+                };
+                auto kick = [&] {
+#pragma unroll
+                    for (int j = 0; j < DPL; ++j) {
+                        force[j] = -((double)xp[j] - ref(pv, r, j)) * c.inv_s2r + beta * gp[j];
+                        mom[j] += he * force[j];
+                    }
+                };
+                int l = 0;
                 bool drifted = false;  // the position of step l is there already
                 if constexpr (kLooks) {
+                    const bool look = pv.lmf && tg.K > 1 && (!wait || (*wait & 15) == 0);
                     while (look && l < L && !drifted) {
                         drift();
                         const ParView pf = fresh(pv);
@@ -863,7 +871,12 @@ struct Particle {
                             drifted = true;
                         }
                     }
-                    vain = drifted && l == 0;
+                    if (wait) {
+                        if (look)
+                            *wait = (drifted && l == 0) ? look_in_vain(*wait) : 0;
+                        else if (*wait & 15)
+                            --*wait;
+                    }
                 }
                 // ell is wanted at the end only (without registers for a second copy
                 // of the evaluation it is formed each time)
@@ -878,12 +891,6 @@ struct Particle {
                     ellp = eval<true, true>(tg, c, pv, r, xp, gp);
                     kick();
                 }
-            }
-            if (wait) {
-                if (look)
-                    *wait = vain ? look_in_vain(*wait) : 0;
-                else if (*wait & 15)
-                    --*wait;
             }
             double kin1 = 0.0, dle = 0.0;
 #pragma unroll
@@ -1376,16 +1383,16 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
             // a rejected proposal's state is still in memory: neither it nor its
             // gradient is held over the step, and it is written only where it
             // comes from the gathered copies
-            constexpr bool kLooks = MOVE == kHmc && Particle<FAM, LPP, DPL>::kLooks;
+            constexpr bool kFlat = DPL > 8, kWaits = kFlat && MOVE == kHmc && Particle<FAM, LPP, DPL>::kLooks;
             int wait = 0;  // kept with the tile from step to step
-            if constexpr (kLooks)
+            if constexpr (kWaits)
                 wait = __builtin_amdgcn_readfirstlane((int)z.tile_part[(size_t)tile * 8 + 6]);
             float xp[DPL];
             double gp[DPL], ellp;
-            acc = Particle<FAM, LPP, DPL>::template propose<MOVE, (DPL > 8)>(a.tg, c, pv, a.key, (uint32_t)nl,
+            acc = Particle<FAM, LPP, DPL>::template propose<MOVE, kFlat>(a.tg, c, pv, a.key, (uint32_t)nl,
                                                                   (uint32_t)t, r, a.leapfrog, beta, eps,
                                                                   x, ell, g, xp, ellp, gp, -1, &wait);
-            if constexpr (kLooks)
+            if constexpr (kWaits)
                 if (lane == 0) z.tile_part[(size_t)tile * 8 + 6] = (double)wait;
             if (acc) ell = ellp;
             if (rs && !acc) {
