@@ -1131,7 +1131,9 @@ hipError_t launch_target_eval(const EvalArgs& E, const ValuShape& s, hipStream_t
     return dispatch_all(6, E.a, s, 0, nullptr, 0, st, nullptr, &E);
 }
 
-// Sum over the workgroup, in a fixed order (every thread gets it).
+// Sum over the workgroup, in a fixed order (every thread gets it): pairwise over the
+// lanes and over the waves.  (The waves one after the other leave more rounding:
+// rejuvenation's averages 3.6e-16 off instead of 3.1e-16.)
 template <int THREADS>
 __device__ __forceinline__ double block_sum(double v, double* shw)
 {
@@ -1140,10 +1142,7 @@ __device__ __forceinline__ double block_sum(double v, double* shw)
     __syncthreads();  // shw may still be read from an earlier sum
     if (threadIdx.x % kWave == 0) shw[threadIdx.x / kWave] = v;
     __syncthreads();
-    double s = shw[0];
-#pragma unroll
-    for (int i = 1; i < W; ++i) s += shw[i];
-    return s;
+    return group_sum<W>(shw[threadIdx.x % W]);
 }
 
 // Column b of the tile sums over tiles in a fixed order.  Bound by the latency of
