@@ -313,8 +313,10 @@ struct Particle {
     // trajectories of the sweeps, whose two waves per SIMD leave registers: 24 HMC steps
     // of 5 leapfrog steps of 20011 overlapping particles, d = 100, 8 components, 1.78 ->
     // 1.53 ms; 3 leapfrog steps of 70000 at d = 30, 2.04 -> 1.65 ms.  The per-step kernel's three
-    // waves spill (12.4 -> 15.1 ms for 96 steps of 65536 particles), and a MALA step,
-    // one evaluation, is 5 to 12% slower flat.
+    // waves spill (12.4 -> 15.1 ms for 96 steps of 65536 particles).  A MALA step, one
+    // evaluation, gains with lanes of 16 coordinates in the sweeps (16 steps of 60000
+    // particles, 16 components, d = 50 1.19 -> 0.91 ms), loses in the per-step kernel
+    // (d = 200, N = 30000 2.28 -> 2.87 ms) and with fewer coordinates (5 to 12%).
     template <bool GRAD, bool FLAT>
     static __device__ __forceinline__ double mixture_multilane(const TargetDev& tg, const Consts& c,
                                                                const ParView& pv, int r,
@@ -790,7 +792,7 @@ struct Particle {
                 const double rr = (double)xp[j] - xv - h * ga;
                 fwd = fma(rr, rr, fwd);
             }
-            ellp = eval<true>(tg, c, pv, r, xp, gp);
+            ellp = eval<true, FLAT && !kRoomy>(tg, c, pv, r, xp, gp);
 #pragma unroll
             for (int j = 0; j < DPL; ++j) {
                 const double xv = (double)x[j];
@@ -1383,7 +1385,8 @@ __global__ void __launch_bounds__(256, (MinWaves<FAM, MOVE, DPL>::value))
             // a rejected proposal's state is still in memory: neither it nor its
             // gradient is held over the step, and it is written only where it
             // comes from the gathered copies
-            constexpr bool kFlat = DPL > 8, kWaits = kFlat && MOVE == kHmc && Particle<FAM, LPP, DPL>::kLooks;
+            constexpr bool kFlat = MOVE == kHmc && DPL > 8;
+            constexpr bool kWaits = kFlat && Particle<FAM, LPP, DPL>::kLooks;
             int wait = 0;  // kept with the tile from step to step
             if constexpr (kWaits)
                 wait = __builtin_amdgcn_readfirstlane((int)z.tile_part[(size_t)tile * 8 + 6]);
